@@ -59,7 +59,7 @@ def listed():
         _case("index_1m", "index", blocks=65536),
         # the index of the blocks that a 32K-token prefill adds to a history, from keys with RoPE
         _case("index_rope_32k", "index_rope", blocks=18331, first=16283),
-        # a recall point's working-set update: a 64K view over a pool of twice its pages
+        # a recall point's working-set update: a 64K view over a pool of 80K tokens
         _case("working_set_64k", "working_set", bt=32, blocks=32768, view=2048),
         # a 128K view laid out anew
         _case("materialize_128k", "materialize", bt=32, blocks=32768, view=4096),
@@ -231,7 +231,7 @@ def _views(c, seed):
 
 
 def _exec_pages(c):
-    return 2 * c["view"]
+    return c["view"] + max(1, c["view"] // 4)
 
 
 # ---- the calls --------------------------------------------------------------
@@ -365,7 +365,7 @@ def tolerance(case):
     if kind in ("working_set", "materialize"):  # re-encoded keys, rounded to the pool's type: 2e-3, fp32 7e-8
         return {"rel": 8e-3, "max": 5e-2} if dtype == "bf16" else {"rel": 3e-7}
     if kind == "recall":
-        return {"rel": 2e-7, "differ": 0.01}  # 3e-8 to 6e-8
+        return {"rel": 1e-6, "differ": 0.01}  # 3e-8 (mean) to 2e-7 (max)
     return {"rel": 2e-5, "differ": 0.01}  # 1e-6 to 5e-6 (out; clustered keys the most)
 
 
