@@ -11,6 +11,7 @@ namespace kvmem {
 
 constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLog2eLo = (float)(1.4426950408889634 - (double)kLog2e);  // log2(e) beyond the fp32 value
 constexpr float kLn2 = 0.6931471805599453f;
 
 // 16-byte load of data read exactly once per step (K/V pages, raw keys): the

@@ -36,10 +36,14 @@ constexpr int kScoreVectorRows = 8;
 // The 16-row kernel's waves are persistent: about kMfma16Waves of them over
 // all (layer, KV head) pairs, four per workgroup, each leaving one partial.
 constexpr int kMfma16Waves = 2048;
-// More than 16 query rows per KV head (a recall point's prefill query): one
-// workgroup per index tile runs every row of its (layer, KV head) in chunks of
-// 16 on the matrix cores; the block relevance then sums the rows in
-// partitions of about kReduceRowsPerPart rows (at most kReduceMaxParts).
+// More than 16 query rows per KV head (a recall point's prefill query): a
+// workgroup takes up to 256 of a (layer, KV head)'s rows over a run of index
+// tiles, about kRowsTargetGroups workgroups in all (two rounds of one per
+// compute unit: long enough runs to spread the conversion of the queries,
+// short enough that the last round is not nearly empty); the block relevance
+// then sums the rows in partitions of about kReduceRowsPerPart rows (at most
+// kReduceMaxParts).
+constexpr int kRowsTargetGroups = 512;
 constexpr int kRowsMaxPerHead = 4096;
 constexpr int kReduceRowsPerPart = 512;
 constexpr int kReduceMaxParts = 64;
@@ -109,9 +113,15 @@ inline void plan_select_layout(SelectPlan &p) {
     p.n_rows = p.n_layers * p.n_q * p.n_q_heads;
     p.tile_lo = p.n_sink / kIndexTile;
     p.n_tiles = (int)index_tiles(p.n_blocks - p.n_recent) - p.tile_lo;
+    int parts_cap = 0;  // partials per row that the workspace holds, where more than are used
     if (p.rows_per_head > 16) {
-        p.tiles_per_part = 1;
-        p.n_parts = p.n_tiles;
+        const int per_group = 32 * (p.rows_per_head > 128 ? 8 : p.rows_per_head > 64 ? 4 : p.rows_per_head > 32 ? 2 : 1);
+        const long long wgs = (long long)p.n_layers * p.n_kv_heads * ((p.rows_per_head + per_group - 1) / per_group);
+        p.tiles_per_part = (int)((wgs * p.n_tiles + kRowsTargetGroups - 1) / kRowsTargetGroups);
+        if (p.tiles_per_part > p.n_tiles) p.tiles_per_part = p.n_tiles;
+        if (p.tiles_per_part < 1) p.tiles_per_part = 1;
+        p.n_parts = (p.n_tiles + p.tiles_per_part - 1) / p.tiles_per_part;
+        parts_cap = p.n_tiles;
     } else if (p.rows_per_head > kScoreVectorRows) {  // persistent waves: n_parts = 4 x workgroups
         const int heads = p.n_layers * p.n_kv_heads;
         int wg = (kMfma16Waves / 4 + heads - 1) / heads;
@@ -133,10 +143,11 @@ inline void plan_select_layout(SelectPlan &p) {
     }
     p.cand_stride = (p.n_cand + 63) / 64 * 64;
     p.n_chunks = (p.n_cand + kSelChunk - 1) / kSelChunk;
+    if (parts_cap < p.n_parts) parts_cap = p.n_parts;
     size_t o = 0;
     p.off_logits = o; o = align_up(o + sizeof(float) * (size_t)p.n_rows * p.cand_stride);
-    p.off_tmax = o;   o = align_up(o + sizeof(float) * (size_t)p.n_rows * p.n_parts);
-    p.off_tsum = o;   o = align_up(o + sizeof(double) * (size_t)p.n_rows * p.n_parts);
+    p.off_tmax = o;   o = align_up(o + sizeof(float) * (size_t)p.n_rows * parts_cap);
+    p.off_tsum = o;   o = align_up(o + sizeof(double) * (size_t)p.n_rows * parts_cap);
     p.off_rmax = o;   o = align_up(o + sizeof(float) * (size_t)p.n_rows);
     p.off_rinvz = o;  o = align_up(o + sizeof(double) * (size_t)p.n_rows);
     p.off_r32 = o;    o = align_up(o + sizeof(float) * (size_t)p.n_sel * p.cand_stride);

@@ -246,109 +246,438 @@ __global__ __launch_bounds__(kScoreThreads) void score_logits_mfma16_kernel(
 }
 
 // More than 16 query rows per KV head (a recall point: the prefill's query
-// tokens x the group's heads; a ragged last 16-row chunk repeats its last row,
-// whose copies are never written).  The scoring is then a dense contraction,
-// S = Q index^T, run on the fp64 matrix cores for the same reason as above.
-// One workgroup per (index tile, KV head, layer): the tile's 64 x D floats are
-// staged in LDS once and serve every row of that (layer, KV head); each wave
-// takes 16-row chunks in turn.  Per chunk and 16-dim slice c, lane l (r16 =
-// l % 16, kg = l / 16) holds the 4 dims 16c + 4kg .. of query row r16 (A
-// operand) and of block 16gb + r16 (B operand, gb = 0..3); contraction slot kg
-// stands for those dims on both sides.  Lane l receives the logits of rows
-// kg + 4i of the chunk for block 16gb + r16, so every row's 64 logits sit in
-// the 16 lanes of one kg group, which also reduce its (max, sum of exp).
-template <int D>
-__global__ __launch_bounds__(kScoreThreads) void score_logits_rows_kernel(
+// tokens x the group's heads): the scoring is a dense contraction S = index Q^T
+// whose logits must be the fp32 rounding of the dot products (see above).  It
+// runs on the int8 matrix cores (64 times the fp64 rate), with exact sums: a
+// row (query or block) is scaled by a power of two so that its largest element
+// is below 1 and rounded to 31-bit fixed point, the fixed-point value is split
+// into four balanced base-256 digits (d0 of 7 bits, d1..d3 of 8), and
+//   q . x = 2^(eq + ex - 12) sum_{i + j <= 3} 256^-(i + j) (q_i . x_j)
+// keeps the ten digit products of weight 256^-3 or more (a fixed-point value is
+// 2^24 times the sum of its digits over 256^i).  Every digit product
+// and its sum over d <= 128 dims is exact in int32 (below 2^23), products of one weight share
+// an accumulator, and the four accumulators are joined exactly in fp64.
+// What is dropped: elements more than 7 binades below their row's largest lose
+// bits below 2^-31 of it, and the six smallest digit products contribute
+// about 2^-27 of |q|max |x|max -- 20 times below the fp32 rounding that the
+// logit takes anyway (measured: the logits' error against fp64 is that of
+// correctly rounded logits).  Rows with an infinity or a NaN take a plain fp64 dot
+// product per logit instead.
+//
+// Blocking.  A wave keeps the digits of 32 query rows in registers (64 VGPRs at
+// d = 128) for its whole life; WR such waves (times WC column halves) share the
+// digits of a 64-block index tile, which the workgroup converts once into one
+// of NB LDS stages.  The tile is the A operand (v_mfma_i32_16x16x64_i8, lane:
+// block l % 16 of a 16-block group, 16 dims), the queries are B, so that a lane
+// ends with four blocks' logits of two query rows and keeps those rows' softmax
+// sums by itself: no cross-lane work until the wave's end.  A wave's logits of
+// the tile go through LDS so that every store covers whole lines.
+// With two stages a tile takes one barrier: its elements are loaded two tiles
+// ahead, their maxima put in LDS one tile ahead, and one half of the waves
+// converts the next tile before its products, the other half in the middle of
+// them, so that the matrix cores always have a wave to serve.
+// What bounds it: the vector units.  A 16-block group takes a wave 40 products
+// (640 cycles of the matrix cores) and about 230 vector instructions (join,
+// exponential, fp64 sum, its share of the conversion); in counters the vector
+// units issue 68% of the cycles and the matrix cores work 40%.  A 1M-token
+// recall (16,384 rows x 32,512 blocks x 128 dims, 2.13 GB of logits written)
+// takes 925 us; the fp64 matrix cores took 2,644.  Measured and not kept: the
+// next group's products issued among the join of the current one (37 to 53
+// spilled registers, 1,370 us); 16 rows a wave with four waves per SIMD (985);
+// raised wave priorities in either phase (940 to 970); non-temporal stores (955).
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kDigitExpBad = INT32_MAX;  // exponent mark of a row that holds an infinity or a NaN
+
+__device__ inline uint32_t abs_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+// Exponent e with |x| < 2^e for every element of a row whose largest absolute
+// value has the bits m (0 for a row of zeros), and whether the row is finite.
+__device__ inline int row_exponent(uint32_t m) { return __builtin_amdgcn_frexp_expf(__uint_as_float(m)); }
+__device__ inline bool row_finite(uint32_t m) { return m < 0x7f800000u; }
+
+// The four balanced base-256 digits of round(x 2^(30 - e)), |x| < 2^e, as the
+// bytes of one word (byte 3 is the leading digit): adding 0x80 to the three low
+// bytes makes their values offset-binary, flipping their top bits makes them two's complement.
+__device__ inline uint32_t digits_of(float x, int e) {
+    const int v = (int)__builtin_rintf(ldexpf(x, 30 - e));
+    return ((uint32_t)v + 0x00808080u) ^ 0x00808080u;
+}
+// Byte p of four words, packed (word i at byte i): the digits of 4 dims of one plane.
+__device__ inline uint32_t plane_of(const uint32_t (&w)[4], int p) {
+    const uint32_t lo = __builtin_amdgcn_perm(w[1], w[0], 0x0c0c0000u | (uint32_t)((4 + p) << 8) | (uint32_t)p);
+    const uint32_t hi = __builtin_amdgcn_perm(w[3], w[2], 0x00000c0cu | (uint32_t)((4 + p) << 24) | (uint32_t)(p << 16));
+    return lo | hi;
+}
+// 16 dims -> one 16-byte operand slice per digit plane (plane 0: leading digits)
+__device__ inline void digit_planes(const float4 (&x)[4], int e, i32x4_t (&d)[4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const uint32_t w[4] = {digits_of(x[v].x, e), digits_of(x[v].y, e), digits_of(x[v].z, e),
+                               digits_of(x[v].w, e)};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) d[p][v] = (int)plane_of(w, 3 - p);
+    }
+}
+__device__ inline uint32_t max_abs_bits(const float4 (&x)[4]) {
+    uint32_t m = 0u;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        m = max(m, max(max(abs_bits(x[v].x), abs_bits(x[v].y)), max(abs_bits(x[v].z), abs_bits(x[v].w))));
+    return m;
+}
+// Adds n * 2^20 to the high word of a double: times 2^n while the result stays normal.
+__device__ inline double scale_exp(double x, int n20) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    return __longlong_as_double((int64_t)(((uint64_t)((uint32_t)(b >> 32) + (uint32_t)n20) << 32) | (uint32_t)b));
+}
+// How far a logit may lie above the reference of its row's running sum before
+// the reference moves up to it: e^16 is far from overflow, and the first tile's
+// maximum is almost always close enough to stay.
+constexpr float kRefSlack = 16.f;
+
+// e^x for x <= kRefSlack, x below -86 counting as -86: x log2(e) is split into
+// an integer, which is added to the exponent bits, and a rest in [-1/2, 1/2]
+// formed with fused multiply-adds (no error beyond v_exp_f32's own).
+__device__ inline float exp_sum_term(float x) {
+    x = fmaxf(x, -86.f);
+    const float m = fmaf(x, kLog2e, 12582912.f), r = m - 12582912.f;  // 1.5 * 2^23: r = round(x log2(e))
+    const float a = fmaf(x, kLog2eLo, fmaf(x, kLog2e, -r));
+    return __uint_as_float(__float_as_uint(exp2_hw(a)) + (__float_as_uint(m) << 23));
+}
+
+template <int D, int WR, int WC, int NB>
+__global__ __launch_bounds__(kWave *WR *WC, 2) void score_logits_i8_kernel(
     const float *__restrict__ q, const float *__restrict__ index, int n_blocks, int n_kv_heads,
     int n_q_heads, int group, int n_q, int n_sink, int n_cand, int64_t cand_stride, int tile_lo,
-    int n_parts, float scale, float *__restrict__ logits, float *__restrict__ tmax,
-    double *__restrict__ tsum) {
-    constexpr int NW = kScoreThreads / kWave, NC = D / 16;
-    __shared__ float4 sm_idx[D / 4][kIndexTile];  // the tile in its stored layout: [j4][block]
+    int n_tiles, int tiles_per_wg, int n_parts, float scale, float *__restrict__ logits,
+    float *__restrict__ tmax, double *__restrict__ tsum) {
+    constexpr int NT = kWave * WR * WC, KS = D / 64, NG = D / 16;
+    constexpr int UNITS = NG * kIndexTile, UPT = (UNITS + NT - 1) / NT;  // (16 dims, block) units per thread
+    constexpr int NGRP = 4 / WC;            // 16-block groups of the tile per wave
+    constexpr int WCOL = kIndexTile / WC;   // blocks of the tile per wave
+    constexpr int OP = WCOL + 4;            // row pitch of the logits' LDS tile, in floats
+    static_assert(WC == 1 || WC == 2, "a tile has two 32-block halves");
+    // the next tile's elements are held in registers, unless the few threads of the
+    // smallest workgroup would hold 64 for it (several of them share a unit instead)
+    constexpr bool AHEAD = UPT <= 2;
+    __shared__ i32x4_t sm_d[NB][4][NG][kIndexTile];  // digit planes of the tile, 16 dims per entry
+    __shared__ uint32_t sm_max[NB][NG][kIndexTile];
+    __shared__ __attribute__((aligned(16))) int32_t sm_e[NB][kIndexTile];  // (block exponents - 30) << 20, or kDigitExpBad
+    __shared__ __attribute__((aligned(16))) float sm_o[WR * WC][32 * OP];  // a wave's logits of the tile
+    __shared__ int32_t sm_finite[NB];  // every block of the tile is finite
+    __shared__ int64_t sm_row[WR * 32];  // offsets of the rows' logits
+    __shared__ float sm_m[WC][WR * 32];
+    __shared__ double sm_s[WC][WR * 32];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int wr = wave % WR, wc = wave / WR;
     const int r16 = lane % 16, kg = lane / 16;
-    const int g = blockIdx.y, l = blockIdx.z;
-    const int tile = tile_lo + blockIdx.x;
-    {
-        const int64_t tiles_per_layer = index_tiles(n_blocks);
-        const float4 *src = reinterpret_cast<const float4 *>(
-            index + (((int64_t)l * tiles_per_layer + tile) * n_kv_heads + g) * (int64_t)(D / 4) * (kIndexTile * 4));
-        for (int i = threadIdx.x; i < (D / 4) * kIndexTile; i += kScoreThreads)
-            sm_idx[i / kIndexTile][i % kIndexTile] = src[i];
+    const int g = blockIdx.y % n_kv_heads, rg = blockIdx.y / n_kv_heads, l = blockIdx.z;
+    const int rows = group * n_q;
+    const int row0 = (rg * WR + wr) * 32;  // the wave's first row of the head
+    const bool active = row0 < rows;       // (wave-uniform) an empty wave only helps to convert tiles
+    // rows past the head's last repeat it (and write the same logits to the same place)
+    auto row_at = [&](int i) {
+        const int rr = min(row0 + i, rows - 1);
+        return ((int64_t)l * n_q + rr / group) * n_q_heads + g * group + rr % group;
+    };
+    const int64_t tiles_per_layer = index_tiles(n_blocks);
+    const int t_lo = blockIdx.x * tiles_per_wg, t_hi = min(n_tiles, t_lo + tiles_per_wg);
+
+    const float *base = index + ((int64_t)l * tiles_per_layer * n_kv_heads + g) * (int64_t)(D / 4) * (kIndexTile * 4);
+    auto tile_src = [&](int t) {
+        return base + (int64_t)(tile_lo + t) * n_kv_heads * (D / 4) * (kIndexTile * 4);
+    };
+    // unit u: dims 16 * (u / 64) .. of block u % 64; a wave's load covers 1 KB
+    float4 raw[UPT][4];
+    auto load = [&](int t) {  // t clamped into the run: every load is unconditional
+        const float *src = tile_src(min(t, t_hi - 1));
+#pragma unroll
+        for (int k = 0; k < UPT; ++k) {
+            const int u = min((int)threadIdx.x + NT * k, UNITS - 1);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                raw[k][v] = *reinterpret_cast<const float4 *>(
+                    src + (4 * (u / kIndexTile) + v) * (kIndexTile * 4) + (u % kIndexTile) * 4);
+        }
+    };
+    auto put_max = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < UPT; ++k) {
+            const int u = threadIdx.x + NT * k;
+            if (UNITS % NT == 0 || u < UNITS) sm_max[buf][u / kIndexTile][u % kIndexTile] = max_abs_bits(raw[k]);
+        }
+    };
+    auto put_digits = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < UPT; ++k) {
+            const int u = threadIdx.x + NT * k, ng = u / kIndexTile, b = u % kIndexTile;
+            if (UNITS % NT != 0 && u >= UNITS) break;
+            uint32_t m = 0u;
+#pragma unroll
+            for (int i = 0; i < NG; ++i) m = max(m, sm_max[buf][i][b]);
+            const int e = row_exponent(m);
+            i32x4_t d[4];
+            digit_planes(raw[k], e, d);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) sm_d[buf][p][ng][b] = d[p];
+            if (ng == 0) {  // a whole wave: the 64 blocks of the tile
+                sm_e[buf][b] = row_finite(m) ? (e - 30) * (1 << 20) : kDigitExpBad;
+                const bool all = __all(row_finite(m));
+                if (b == 0) sm_finite[buf] = all;
+            }
+        }
+    };
+
+    load(t_lo);
+    // the digits of the wave's 32 rows: lane holds, of rows r16 and 16 + r16, dims
+    // 64s + 16kg .. + 15 of k-step s
+    i32x4_t qd[2][KS][4];
+    double rscale[2];
+    bool row_bad[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float *qp = q + row_at(16 * h + r16) * D + 16 * kg;
+        float4 x[KS][4];
+        uint32_t m = 0u;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[s][v] = *reinterpret_cast<const float4 *>(qp + 64 * s + 4 * v);
+            m = max(m, max_abs_bits(x[s]));
+        }
+        m = max(m, (uint32_t)__shfl_xor((int)m, 16, kWave));
+        m = max(m, (uint32_t)__shfl_xor((int)m, 32, kWave));
+        const int e = row_exponent(m);
+        row_bad[h] = !row_finite(m);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) digit_planes(x[s], e, qd[h][s]);
+        // logit = (digit sum) 2^(eq - 30) 2^(ex - 30) scale, digit sum = join 2^24
+        rscale[h] = ldexp((double)scale, (row_bad[h] ? 0 : e) - 30 + 24);
+    }
+    if (wc == 0 && lane < 32) sm_row[wr * 32 + lane] = row_at(lane) * cand_stride;
+    put_max(0);
+    __syncthreads();
+    put_digits(0);
+    if constexpr (AHEAD) load(t_lo + 1);
+    if constexpr (NB == 2) {
+        put_max(1);
     }
     __syncthreads();
-    const int64_t b0 = (int64_t)tile * kIndexTile - n_sink;  // candidate of the tile's first block
-    // candidates of this lane's 4 blocks (16gb + r16) that are in C
-    bool cok[4];
+
+    float mref[2] = {-INFINITY, -INFINITY};  // references of the rows' sums, in this lane's blocks
+    double srun[2] = {0.0, 0.0};
+    float *my_o = sm_o[wave];
+    // digit sums of the group at block cb of the tile: acc[h][w], lane: row 16h + r16, blocks cb + 4kg + i
+    auto products = [&](int buf, int cb, i32x4_t (&acc)[2][4]) {
+        i32x4_t a[KS][4];
 #pragma unroll
-    for (int gb = 0; gb < 4; ++gb) cok[gb] = b0 + 16 * gb + r16 >= 0 && b0 + 16 * gb + r16 < n_cand;
-    const int rows = n_q * group;
-    for (int chunk = wave; chunk < (rows + 15) / 16; chunk += NW) {
-        // A operand: query row chunk*16 + r16 of (layer l, KV head g); in a
-        // ragged last chunk the rows past the head's count repeat the last
-        // row and their results are never written
-        const int r = min(chunk * 16 + r16, rows - 1);
-        const int64_t qrow = ((int64_t)l * n_q + r / group) * n_q_heads + g * group + r % group;
-        f64x4_t st[4];
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int gb = 0; gb < 4; ++gb) st[gb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        float4 qa[NC];  // the chunk's query slices, all in flight before the products start
+            for (int p = 0; p < 4; ++p) a[s][p] = sm_d[buf][p][4 * s + kg][cb + r16];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) qa[c] = *reinterpret_cast<const float4 *>(q + qrow * D + 16 * c + 4 * kg);
-        float4 bn[4];
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int gb = 0; gb < 4; ++gb) bn[gb] = sm_idx[kg][16 * gb + r16];
+            for (int w = 0; w < 4; ++w) acc[h][w] = i32x4_t{0, 0, 0, 0};
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            float4 bv[4];
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-            for (int gb = 0; gb < 4; ++gb) bv[gb] = bn[gb];
-            if (c + 1 < NC) {
+            for (int p = 0; p < 4; ++p)
 #pragma unroll
-                for (int gb = 0; gb < 4; ++gb) bn[gb] = sm_idx[4 * (c + 1) + kg][16 * gb + r16];
+                for (int w = 3; w >= p; --w)  // an accumulator comes back after at least four others
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        acc[h][w] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[s][p], qd[h][s][w - p], acc[h][w], 0, 0, 0);
+    };
+    auto join = [&](int buf, int cb, const i32x4_t (&acc)[2][4], float (&sv)[2][4]) {
+        const i32x4_t e4 = *reinterpret_cast<const i32x4_t *>(&sm_e[buf][cb + 4 * kg]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double hi = (double)(acc[h][0][i] * 256 + acc[h][1][i]);
+                const double lo = (double)(acc[h][2][i] * 256 + acc[h][3][i]);
+                sv[h][i] = (float)(fma(hi, 65536.0, lo) * scale_exp(rscale[h], e4[i]));
             }
-            const float av[4] = {qa[c].x, qa[c].y, qa[c].z, qa[c].w};
+    };
+    auto max4 = [](const float (&x)[4]) { return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])); };
+    // moves row h's reference to m
+    auto rebase = [&](int h, float m) {
+        srun[h] = mref[h] == -INFINITY ? (srun[h] == srun[h] ? 0.0 : srun[h]) : srun[h] * exp((double)mref[h] - (double)m);
+        mref[h] = m;
+    };
+    auto add_terms = [&](int h, const float (&sv)[4]) {
+        const float mr = mref[h] == -INFINITY ? 0.f : mref[h];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+        for (int i = 0; i < 4; ++i) srun[h] += (double)exp_sum_term(sv[i] - mr);
+    };
+    // One tile, any tile: groups in turn, every special case handled where it
+    // shows (blocks outside C, rows that are not finite, a growing reference).
+    auto tile_any = [&](int t, int buf) {
+        const int64_t c_wave = (int64_t)(tile_lo + t) * kIndexTile + WCOL * wc - n_sink;
+#pragma unroll 1
+        for (int grp = 0; grp < NGRP; ++grp) {
+            const int cb = WCOL * wc + 16 * grp;
+            i32x4_t acc[2][4];
+            float sv[2][4];
+            products(buf, cb, acc);
+            join(buf, cb, acc, sv);
+            bool bad = row_bad[0] || row_bad[1];
 #pragma unroll
-                for (int gb = 0; gb < 4; ++gb) {
-                    const float be = e == 0 ? bv[gb].x : e == 1 ? bv[gb].y : e == 2 ? bv[gb].z : bv[gb].w;
-                    st[gb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[e], (double)be, st[gb], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) bad |= sm_e[buf][cb + 4 * kg + i] == kDigitExpBad;
+            if (__any(bad)) {  // an infinity or NaN in a row: the plain sums
+                const float *src = tile_src(t);
+#pragma unroll 1
+                for (int k = 0; k < 8; ++k) {
+                    const int h = k / 4, b = cb + 4 * kg + k % 4;
+                    if (!((h ? row_bad[1] : row_bad[0]) || sm_e[buf][b] == kDigitExpBad)) continue;
+                    const float *qp = q + row_at(16 * h + r16) * D;
+                    double dot = 0.0;
+                    for (int j = 0; j < D; ++j)
+                        dot += (double)qp[j] * (double)src[(j / 4) * (kIndexTile * 4) + b * 4 + j % 4];
+                    const float sd = (float)(dot * (double)scale);
+                    const int64_t c = c_wave + 16 * grp + 4 * kg + k % 4;
+#pragma unroll
+                    for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sv[hh][i] = 4 * hh + i == k ? sd : sv[hh][i];
+                        // +inf and NaN make the row's sum NaN, as e^(s - max) does
+                        if (hh == h && c >= 0 && c < n_cand && !(sd < INFINITY)) srun[hh] = __builtin_nan("");
+                    }
                 }
-            __builtin_amdgcn_sched_barrier(0);  // next slice's LDS reads overlap these products, no further
+            }
+            const int64_t c0 = c_wave + 16 * grp + 4 * kg;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float *dst = logits + sm_row[wr * 32 + 16 * h + r16] + c0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = c0 + i >= 0 && c0 + i < n_cand;
+                    if (ok) dst[i] = sv[h][i];
+                    sv[h][i] = ok ? sv[h][i] : -INFINITY;  // not in C: adds nothing
+                }
+                const float gm = max4(sv[h]);
+                if (gm > mref[h] + kRefSlack) rebase(h, gm);
+                add_terms(h, sv[h]);
+            }
         }
-        // lane: rows kg + 4i of the chunk, blocks 16gb + r16
+    };
+    // A tile of finite rows whose blocks are all candidates: no special case
+    // inside, the stores on no branch (behind one, the wait for the next tile's
+    // elements would also wait for the stores: 310 us at 1M).  convert(grp)
+    // runs before each group.
+    auto tile_full = [&](int t, int buf, auto convert) {
+        const int64_t c_wave = (int64_t)(tile_lo + t) * kIndexTile + WCOL * wc - n_sink;
+        float tm[2] = {-INFINITY, -INFINITY};
+        if (t == t_lo) {  // the first tile's first group sets the references
+            i32x4_t acc[2][4];
+            float sv[2][4];
+            products(buf, WCOL * wc, acc);
+            join(buf, WCOL * wc, acc, sv);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int rr0 = chunk * 16 + kg + 4 * i;
-            const bool rok = rr0 < rows;  // the same in the 16 lanes that share this row
-            const int rr = rok ? rr0 : rows - 1;
-            const int64_t row = ((int64_t)l * n_q + rr / group) * n_q_heads + g * group + rr % group;
-            float sv[4];
-            float mx = -INFINITY;
+            for (int h = 0; h < 2; ++h) mref[h] = max4(sv[h]);
+        }
+        const double s_was[2] = {srun[0], srun[1]};
+#pragma unroll 1
+        for (int grp = 0; grp < NGRP; ++grp) {
+            convert(grp);
+            const int cb = WCOL * wc + 16 * grp;
+            i32x4_t acc[2][4];
+            float sv[2][4];
+            products(buf, cb, acc);
+            join(buf, cb, acc, sv);
 #pragma unroll
-            for (int gb = 0; gb < 4; ++gb) {
-                sv[gb] = (float)(st[gb][i] * (double)scale);
-                if (cok[gb]) {
-                    if (rok) logits[row * cand_stride + b0 + 16 * gb + r16] = sv[gb];
-                    mx = fmaxf(mx, sv[gb]);
+            for (int h = 0; h < 2; ++h) {
+                *reinterpret_cast<float4 *>(my_o + (16 * h + r16) * OP + 16 * grp + 4 * kg) =
+                    make_float4(sv[h][0], sv[h][1], sv[h][2], sv[h][3]);
+                tm[h] = fmaxf(tm[h], max4(sv[h]));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) srun[h] += (double)exp_sum_term(sv[h][i] - mref[h]);
+            }
+        }
+        constexpr int LPR = WCOL / 4, RPI = kWave / LPR;  // lanes per row, rows per store
+#pragma unroll
+        for (int k = 0; k < 32 / RPI; ++k) {
+            const int r = k * RPI + lane / LPR, cc = 4 * (lane % LPR);
+            const float4 v = *reinterpret_cast<const float4 *>(my_o + r * OP + cc);
+            *reinterpret_cast<f32x4u_t *>(logits + sm_row[wr * 32 + r] + c_wave + cc) = f32x4u_t{v.x, v.y, v.z, v.w};
+        }
+        if (__any(tm[0] > mref[0] + kRefSlack || tm[1] > mref[1] + kRefSlack)) {
+            // a reference fell behind (its terms may have overflowed): the tile's sums again, from the logits in LDS
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                srun[h] = s_was[h];
+                if (tm[h] > mref[h] + kRefSlack) rebase(h, tm[h]);
+#pragma unroll 1
+                for (int grp = 0; grp < NGRP; ++grp) {
+                    const float4 v = *reinterpret_cast<const float4 *>(my_o + (16 * h + r16) * OP + 16 * grp + 4 * kg);
+                    const float sv[4] = {v.x, v.y, v.z, v.w};
+                    add_terms(h, sv);
                 }
             }
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, shfl_xor_f(mx, o));
-            double e = 0.0;
-            if (mx != -INFINITY) {
-#pragma unroll
-                for (int gb = 0; gb < 4; ++gb)
-                    if (cok[gb]) e += (double)expf(sv[gb] - mx);
-            }
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) e += __shfl_xor(e, o, kWave);
-            if (r16 == 0 && rok) {
-                tmax[row * n_parts + blockIdx.x] = mx;
-                tsum[row * n_parts + blockIdx.x] = e;
-            }
         }
+    };
+    // tiles whose blocks are all candidates: [f_lo, f_hi); outside them at most
+    // one tile at either end of the row
+    const int f_lo = n_sink > tile_lo * kIndexTile ? 1 : 0;
+    const int f_hi = (int)((n_sink + (int64_t)n_cand) / kIndexTile) - tile_lo;
+    const bool rows_bad = __any(row_bad[0] || row_bad[1]);
+    const bool late = wave >= WR * WC / 2;  // this wave converts the next tile in the middle of the products
+    for (int t = t_lo; t < t_hi; ++t) {
+        const int buf = NB == 2 ? (t - t_lo) & 1 : 0;
+        const bool full = active && t >= f_lo && t < f_hi && !rows_bad && sm_finite[buf];
+        auto convert = [&]() {
+            if constexpr (NB == 2) {
+                // raw holds tile t + 1 (past the end the last one again, never used)
+                put_digits(buf ^ 1);
+                load(t + 2);
+            }
+        };
+        if (full) {
+            tile_full(t, buf, [&](int grp) {
+                if (grp == (late ? NGRP / 2 : 0)) convert();
+            });
+        } else {
+            convert();
+            if (active) tile_any(t, buf);
+        }
+        if constexpr (NB == 2) {
+            put_max(buf);
+            __syncthreads();
+        } else if (t + 1 < t_hi) {
+            if constexpr (!AHEAD) load(t + 1);
+            put_max(0);
+            __syncthreads();
+            put_digits(0);
+            if constexpr (AHEAD) load(t + 2);
+            __syncthreads();
+        }
+    }
+    // the four block quarters of a row (lanes r16 + 16kg), then the column waves
+    auto merge = [](float &m, double &s, float m2, double s2) {
+        const float mx = fmaxf(m, m2);
+        double t = 0.0;
+        if (m != -INFINITY) t += s * exp((double)m - (double)mx);
+        if (m2 != -INFINITY) t += s2 * exp((double)m2 - (double)mx);
+        m = mx;
+        s = t;
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        merge(mref[h], srun[h], shfl_xor_f(mref[h], 16), shfl_xor_d(srun[h], 16));
+        merge(mref[h], srun[h], shfl_xor_f(mref[h], 32), shfl_xor_d(srun[h], 32));
+        if (kg == 0) {
+            sm_m[wc][wr * 32 + 16 * h + r16] = mref[h];
+            sm_s[wc][wr * 32 + 16 * h + r16] = srun[h];
+        }
+    }
+    __syncthreads();
+    if (wc == 0 && lane < 32 && row0 + lane < rows) {
+        float m = sm_m[0][wr * 32 + lane];
+        double z = sm_s[0][wr * 32 + lane];
+        if constexpr (WC == 2) merge(m, z, sm_m[1][wr * 32 + lane], sm_s[1][wr * 32 + lane]);
+        tmax[row_at(lane) * n_parts + blockIdx.x] = m;
+        tsum[row_at(lane) * n_parts + blockIdx.x] = z;
     }
 }
 
@@ -385,6 +714,42 @@ __global__ __launch_bounds__(kScoreThreads) void score_stats_kernel(const float 
         for (int w = 0; w < kScoreThreads / kWave; ++w) tot += sm_d[w];
         rmax[row] = mx;
         rinvz[row] = 1.0 / tot;
+    }
+}
+
+// The same for many rows with at most kStatsRowParts partials each (a recall
+// point: 16,384 rows of 8): a workgroup per row would be 16,384 workgroups with
+// 8 busy threads (40 us at 1M, now 6); here 16 rows share one, each merged by a
+// 16-lane DPP row with every partial loaded at once.
+constexpr int kStatsRowParts = 64;
+__global__ __launch_bounds__(kScoreThreads) void score_stats_rows_kernel(
+    const float *__restrict__ tmax, const double *__restrict__ tsum, int n_rows, int n_parts,
+    float *__restrict__ rmax, double *__restrict__ rinvz, uint32_t *__restrict__ hist, int hist_words) {
+    for (int i = blockIdx.x * kScoreThreads + threadIdx.x; i < hist_words; i += gridDim.x * kScoreThreads)
+        hist[i] = 0u;
+    constexpr int PPL = kStatsRowParts / 16;
+    const int row = blockIdx.x * (kScoreThreads / 16) + threadIdx.x / 16, l16 = threadIdx.x % 16;
+    const int64_t at = (int64_t)min(row, n_rows - 1) * n_parts;
+    float tm[PPL];
+    double ts[PPL];
+#pragma unroll
+    for (int u = 0; u < PPL; ++u) {
+        const int k = min(l16 + 16 * u, n_parts - 1);
+        tm[u] = tmax[at + k];
+        ts[u] = tsum[at + k];
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < PPL; ++u) mx = l16 + 16 * u < n_parts ? fmaxf(mx, tm[u]) : mx;
+    mx = row16_max(mx);
+    double z = 0.0;
+#pragma unroll
+    for (int u = 0; u < PPL; ++u)
+        if (l16 + 16 * u < n_parts && tm[u] != -INFINITY) z += ts[u] * exp((double)tm[u] - (double)mx);
+    z = row16_sum_d(z);
+    if (l16 == 0 && row < n_rows) {
+        rmax[row] = mx;
+        rinvz[row] = 1.0 / z;
     }
 }
 
@@ -517,13 +882,13 @@ __global__ __launch_bounds__(kScoreThreads) void score_reduce_kernel(
     }
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     if (c0 < n_cand && rpart) {
-        // the row partitions' partials, in order (slice 0 only)
-        if (rs == 0) {
-            for (int k = 0; k < n_rsplit; ++k) {
-                const double *src = rpart + ((int64_t)k * gridDim.y + sel) * cand_stride + c0;
+        // the row partitions' partials: every 4th to a slice, 8 of them in
+        // flight (one slice taking all in turn was 24 us at 1M with 32 of them)
+#pragma unroll 8
+        for (int k = rs; k < n_rsplit; k += 4) {
+            const double *src = rpart + ((int64_t)k * gridDim.y + sel) * cand_stride + c0;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] = mode == 0 ? acc[e] + src[e] : (src[e] > acc[e] ? src[e] : acc[e]);
-            }
+            for (int e = 0; e < 4; ++e) acc[e] = mode == 0 ? acc[e] + src[e] : (src[e] > acc[e] ? src[e] : acc[e]);
         }
     } else if (c0 < n_cand) {
 #pragma unroll 8
@@ -605,6 +970,18 @@ hipError_t launch_logits(const SelectPlan &p, const float *q, const float *index
     return hipGetLastError();
 }
 
+template <int D, int WR, int WC, int NB>
+hipError_t launch_logits_i8(const SelectPlan &p, const float *q, const float *index, float scale, float *logits,
+                            float *tmax, double *tsum, hipStream_t stream) {
+    const int row_groups = (p.rows_per_head + 32 * WR - 1) / (32 * WR);
+    dim3 grid(p.n_parts, p.n_kv_heads * row_groups, p.n_layers);
+    hipLaunchKernelGGL((score_logits_i8_kernel<D, WR, WC, NB>), grid, dim3(kWave * WR * WC), 0, stream, q, index,
+                       p.n_blocks, p.n_kv_heads, p.n_q_heads, p.group, p.n_q, p.n_sink, p.n_cand,
+                       (int64_t)p.cand_stride, p.tile_lo, p.n_tiles, p.tiles_per_part, p.n_parts, scale, logits, tmax,
+                       tsum);
+    return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_logits_d(const SelectPlan &p, const float *q, const float *index, float scale,
                            float *logits, float *tmax, double *tsum, uint32_t *hist, hipStream_t stream) {
@@ -627,12 +1004,12 @@ hipError_t launch_logits_d(const SelectPlan &p, const float *q, const float *ind
             return hipGetLastError();
         }
         default: {
-            if (p.tiles_per_part != 1) return hipErrorInvalidValue;
-            dim3 grid(p.n_tiles, p.n_kv_heads, p.n_layers);
-            hipLaunchKernelGGL((score_logits_rows_kernel<D>), grid, dim3(kScoreThreads), 0, stream, q, index,
-                               p.n_blocks, p.n_kv_heads, p.n_q_heads, p.group, p.n_q, p.n_sink, p.n_cand,
-                               (int64_t)p.cand_stride, p.tile_lo, p.n_parts, scale, logits, tmax, tsum);
-            return hipGetLastError();
+            // 32-row waves per workgroup by the row count; the fewer there are, the
+            // more workgroups share a compute unit instead
+            if (p.rows_per_head > 128) return launch_logits_i8<D, 8, 1, 2>(p, q, index, scale, logits, tmax, tsum, stream);
+            if (p.rows_per_head > 64) return launch_logits_i8<D, 4, 2, 2>(p, q, index, scale, logits, tmax, tsum, stream);
+            if (p.rows_per_head > 32) return launch_logits_i8<D, 2, 2, 1>(p, q, index, scale, logits, tmax, tsum, stream);
+            return launch_logits_i8<D, 1, 2, 1>(p, q, index, scale, logits, tmax, tsum, stream);
         }
     }
 }
@@ -654,7 +1031,11 @@ hipError_t launch_select(const SelectPlan &p, const float *q, const float *index
         e = p.head_dim == 128 ? launch_logits_d<128>(p, q, index, scale, logits, tmax, tsum, hist, stream)
                               : launch_logits_d<64>(p, q, index, scale, logits, tmax, tsum, hist, stream);
         if (e != hipSuccess) return e;
-        if (!p.fused_stats) {
+        if (!p.fused_stats && p.n_rows >= 1024 && p.n_parts <= kStatsRowParts) {
+            hipLaunchKernelGGL(score_stats_rows_kernel, dim3((p.n_rows + 15) / 16), dim3(kScoreThreads), 0, stream,
+                               tmax, tsum, p.n_rows, p.n_parts, rmax, rinvz, hist, p.n_sel * kSelHistWords);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        } else if (!p.fused_stats) {
             hipLaunchKernelGGL(score_stats_kernel, dim3(p.n_rows), dim3(kScoreThreads), 0, stream, tmax, tsum,
                                p.n_parts, rmax, rinvz, hist, p.n_sel * kSelHistWords);
             if ((e = hipGetLastError()) != hipSuccess) return e;
