@@ -4,8 +4,9 @@
 // Kernels, by shape (launch_bt picks one; every one writes the same partials):
 //   attn_mfma16        bf16 K/V with 3 to 47 query rows per KV head, and FP8
 //                      below 48 rows: both products on the matrix cores
-//   attn_mfma_rows     48 or more rows (bf16, FP8): groups of 16-row waves
-//                      share each K/V tile through LDS
+//   attn_mfma_rows16   48 to 128 rows (bf16, FP8): 16-row waves share each K/V
+//                      tile through LDS
+//   attn_mfma_rows     more rows (bf16, FP8): 32-row waves do
 //   attn_splitk_row16  fp32 K/V at d = 64 with a multiple of 4 rows (a token
 //                      row is one 16-lane DPP row), vector units
 //   attn_splitk        every other shape, vector units
@@ -486,6 +487,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_splitk_row16_kernel(
 // the operand read; V codes are widened before they go to LDS.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kMfmaRows = 16;
 constexpr int kMfmaTile = 32;  // tokens per tile
 
@@ -780,19 +782,17 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_mfma16_kernel(
     }
 }
 
-// Many query rows per KV head (a step's prefill replayed over the view: e.g.
-// 128 tokens x 4 GQA heads = 512 rows).  The workgroup's NW waves each own 16
+// 48 to 128 query rows per KV head.  The workgroup's NW waves each own 16
 // rows and share every 32-token K/V tile: the whole workgroup loads it once
 // into one of two LDS stages (K and V as bf16; FP8 codes widened on the way
-// in), so K/V is read from memory once per 16 NW rows instead of once per 16
-// (at 512 rows: 466 us with 4 waves, 300 with 8, 288 with 16 over a 64K view).
+// in), so K/V is read from memory once per 16 NW rows instead of once per 16.
 // Per tile each wave runs the products of attn_mfma16 with its K operand read
 // from LDS (row pitch D + 8 halves: the 16 rows of one read sit 4 banks apart)
 // and V^T by the transposing reads; each wave keeps its rows' running softmax
 // and writes their partials itself (no merge across waves).
-// NW waves (16 rows each) share one K/V tile: 4, 8 or 16 by the row count
+// NW waves (16 rows each) share one K/V tile: 4 or 8 by the row count
 template <typename T, int D, int BT, int NW>
-__global__ __launch_bounds__(NW * kWave) void attn_mfma_rows_kernel(
+__global__ __launch_bounds__(NW * kWave) void attn_mfma_rows16_kernel(
     const float *__restrict__ q, const T *__restrict__ k_pool, const T *__restrict__ v_pool,
     int64_t n_pages, const int32_t *__restrict__ view_pages, int n_sel, int n_view, int last_page_tokens,
     int n_kv_heads, int n_q_heads, int group, int rows_total, int pages_per_split, int n_splits,
@@ -965,6 +965,235 @@ __global__ __launch_bounds__(NW * kWave) void attn_mfma_rows_kernel(
     }
 }
 
+// Many query rows per KV head (a step's prefill replayed over the view: e.g.
+// 128 tokens x 4 GQA heads = 512 rows).  The workgroup's NW waves each own 32
+// rows and share every K/V tile of TT tokens: the whole workgroup loads it once
+// into one of two LDS stages (K and V as bf16; FP8 codes widened on the way
+// in), so K/V is read from memory once per 32 NW rows.
+// Per 32 tokens a wave runs the products of attn_mfma16 on
+// v_mfma_f32_32x32x16_bf16: S^T = K Q^T (lane: query row l % 32, 16 of the 32
+// tokens, so the row maximum takes one lane exchange) and O^T = V^T P^T, whose
+// P^T operand is the lane's own probabilities: contraction slot (half h = l / 32, j) of
+// 16-token step kk stands for token 16kk + 8(j/4) + 4h + j%4 on both sides, V^T
+// coming from LDS by the transposing reads.  32 rows a wave halve the LDS reads per
+// row against 16 (a wave reads the whole tile), which then need half the
+// matrix cores' cycles.  The running maximum is only a reference: accumulators
+// are rescaled when a row's scores exceed it by 2^kRowSlack, which after the
+// first tiles hardly happens.  Each wave writes its rows' partials itself.
+// What bounds it: the rate at which the card sustains bf16 products.  512 rows x 64K
+// tokens x 8 heads are 275 GFLOP with the hi + lo pairs: 240 us, 1.15 PFLOP/s,
+// where a plain 8192^3 bf16 product of the vendor's library runs at 1.2 (the clock falls
+// to 1.8 GHz in both).  Explicit interleavings of LDS reads, products and softmax, and
+// a barrier in one place for all waves, all measured the same within 3%.  The kernel
+// with 16-row waves and 64 splits took 285 us, and 27 more for its merge.
+// LDS rows: K at pitch D + 8 halves (the 16 rows of a read phase sit 4 banks apart), V at
+// D + 32 (the four token rows of a transposing read, 64 bytes each, on distinct banks).
+constexpr float kRowSlack = 8.f;  // in base 2
+
+__device__ inline f32x16_t mfma32(bf16x8_t a, bf16x8_t b, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// max over the lane pair l, l ^ 32
+__device__ inline float half_max(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <typename T, int D, int BT, int NW, int TT>
+__global__ __launch_bounds__(NW * kWave, 2) void attn_mfma_rows_kernel(
+    const float *__restrict__ q, const T *__restrict__ k_pool, const T *__restrict__ v_pool,
+    int64_t n_pages, const int32_t *__restrict__ view_pages, int n_sel, int n_view, int last_page_tokens,
+    int n_kv_heads, int n_q_heads, int group, int rows_total, int pages_per_split, int n_splits,
+    float qscale, float v_scale, float *__restrict__ part) {
+    constexpr bool F8 = sizeof(T) == 1;
+    constexpr int EPL = 16 / sizeof(T);               // elements per 16-byte load
+    constexpr int KC = D / 16, MB = D / 32, NS = TT / 32;
+    constexpr int KP = D + 8, VP = D + 32;            // LDS row pitches, in halves
+    constexpr int UPR = D / EPL;                      // 16-byte units per token row
+    constexpr int LPT = TT * UPR;                     // units per tile, K or V
+    constexpr int NT = NW * kWave;
+    constexpr int LPL = (LPT + NT - 1) / NT;          // per thread
+    __shared__ __attribute__((aligned(16))) uint16_t sm_k[2][TT * KP];
+    __shared__ __attribute__((aligned(16))) uint16_t sm_v[2][TT * VP];
+    __shared__ int32_t sm_pg[kAttnMaxPages];
+    const int split = blockIdx.x, g = blockIdx.y;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int r32 = lane % 32, half = lane / 32, r16 = lane % 16;
+    const int row0 = blockIdx.z * (NW * 32) + wave * 32;
+    const bool active = row0 < rows_total;  // (wave-uniform) an empty wave only loads
+    const int32_t *vpages = view_pages + (int64_t)(n_sel == 1 ? 0 : g) * n_view;
+    const int p_begin = split * pages_per_split;
+    const int p_end = min(n_view, p_begin + pages_per_split);
+    const int n_tok = (p_end - p_begin) * BT - (p_end == n_view ? BT - last_page_tokens : 0);
+    const int n_tiles = (n_tok + TT - 1) / TT;
+    // an invalid id is never read; the split's partial becomes NaN
+    const bool bad = stage_page_ids<NT>(vpages, p_begin, p_end - p_begin, n_pages, sm_pg);
+    const bool any_bad = __syncthreads_or(bad) != 0;
+
+    // Q^T operand of this wave's 32 rows, hi + lo bf16 (padding rows are zero)
+    bf16x8_t qhi[KC], qlo[KC];
+    {
+        const int row = min(row0 + r32, rows_total - 1), m = row / group, hh = row % group;
+        const float qs = row0 + r32 < rows_total ? qscale : 0.f;
+        const float *qp = q + ((int64_t)m * n_q_heads + g * group + hh) * D + 8 * half;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            const float4 a = *reinterpret_cast<const float4 *>(qp + 16 * c);
+            const float4 b = *reinterpret_cast<const float4 *>(qp + 16 * c + 4);
+            const float x[8] = {a.x * qs, a.y * qs, a.z * qs, a.w * qs, b.x * qs, b.y * qs, b.z * qs, b.w * qs};
+            split_bf16x8(x, qhi[c], qlo[c]);
+        }
+    }
+    f32x16_t acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[mb][i] = 0.f;
+    float mref = -INFINITY, lpart = 0.f;
+
+    // unit u of tile t: token u / UPR, EPL elements at dim EPL * (u % UPR).  A tile
+    // holds whole pages or lies in one, so a unit's place in its page never changes
+    // and a full tile costs one page id and one multiply-add per load.  Tokens
+    // past the split read its last token again and are masked out of the softmax.
+    static_assert(TT % BT == 0 || BT % TT == 0, "tiles and pages nest");
+    const uint32_t page_elems = (uint32_t)(n_kv_heads * BT * D);
+    auto load = [&](int t, const T *pool, uint4 (&x)[LPL]) {
+        const bool whole = t * TT + TT <= n_tok;  // wave-uniform
+#pragma unroll
+        for (int i = 0; i < LPL; ++i) {
+            const int u = min((int)threadIdx.x + NT * i, LPT - 1);
+            int tok = t * TT + u / UPR;
+            if (!whole) tok = min(tok, n_tok - 1);
+            const uint64_t off = (uint64_t)(uint32_t)sm_pg[tok / BT] * page_elems +
+                                 (uint32_t)((g * BT + tok % BT) * D + EPL * (u % UPR));
+            x[i] = load_stream16(pool + off);
+        }
+    };
+    auto stage = [&](uint16_t *dst, int pitch, const uint4 (&x)[LPL]) {
+#pragma unroll
+        for (int i = 0; i < LPL; ++i) {
+            const int u = threadIdx.x + NT * i;
+            if (LPT % NT == 0 || u < LPT) {
+                uint16_t *d = dst + u / UPR * pitch + EPL * (u % UPR);
+                if constexpr (F8) {
+                    uint2 *d2 = reinterpret_cast<uint2 *>(d);
+                    d2[0] = fp8x4_to_bf16x4(x[i].x);
+                    d2[1] = fp8x4_to_bf16x4(x[i].y);
+                    d2[2] = fp8x4_to_bf16x4(x[i].z);
+                    d2[3] = fp8x4_to_bf16x4(x[i].w);
+                } else {
+                    *reinterpret_cast<uint4 *>(d) = x[i];
+                }
+            }
+        }
+    };
+    // Interval t of the workgroup lies between two barriers: in it K(t) and V(t - 1)
+    // are read, and K(t + 1) and V(t) are put where K(t - 1) and V(t - 2) were.
+    uint4 kr[LPL], vr[LPL];
+    auto turn = [&](int t) {  // the end of interval t
+        if (t + 1 < n_tiles) stage(sm_k[(t + 1) & 1], KP, kr);
+        stage(sm_v[t & 1], VP, vr);
+        if (t + 2 < n_tiles) load(t + 2, k_pool, kr);
+        if (t + 1 < n_tiles) load(t + 1, v_pool, vr);
+        __syncthreads();
+    };
+    load(0, k_pool, kr);
+    load(0, v_pool, vr);
+    stage(sm_k[0], KP, kr);
+    if (n_tiles > 1) load(1, k_pool, kr);
+    __syncthreads();
+    // A wave goes through scores (QK), softmax and output (PV) of tile after tile; the
+    // barrier falls between softmax and PV for the first half of the waves and
+    // between QK and softmax for the other half, so that of the two waves of a SIMD one is
+    // in its products while the other is in its softmax (252 against 259 us).
+    const bool late = __builtin_amdgcn_readfirstlane(wave) >= NW / 2;
+    if (active) {
+        for (int t = 0; t < n_tiles; ++t) {
+            const uint16_t *kt = sm_k[t & 1] + r32 * KP + 8 * half;
+            f32x16_t s[NS];
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[n][i] = 0.f;
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    const bf16x8_t kk = as_bf16x8(*reinterpret_cast<const uint4 *>(kt + 32 * n * KP + 16 * c));
+                    s[n] = mfma32(kk, qhi[c], s[n]);
+                    s[n] = mfma32(kk, qlo[c], s[n]);
+                }
+            }
+            if (late) turn(t);
+            // lane: row r32, tokens 32n + 8(i/4) + 4 half + i%4
+            if (t * TT + TT > n_tok) {
+#pragma unroll
+                for (int n = 0; n < NS; ++n)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if (t * TT + 32 * n + 8 * (i / 4) + 4 * half + i % 4 >= n_tok) s[n][i] = -INFINITY;
+            }
+            float cm = s[0][0];
+#pragma unroll
+            for (int n = 0; n < NS; ++n)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) cm = fmaxf(cm, s[n][i]);
+            cm = half_max(cm);
+            if (__any(cm > mref + kRowSlack)) {
+                const float mn = fmaxf(mref, cm);
+                const float alpha = exp2_hw(mref - (mn == -INFINITY ? 0.f : mn));  // 0 while mref is -inf
+                lpart *= alpha;
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) acc[mb] *= alpha;
+                mref = mn;
+            }
+            const float ms = mref == -INFINITY ? 0.f : mref;
+            bf16x8_t phi[2 * NS], plo[2 * NS];
+#pragma unroll
+            for (int n = 0; n < 2 * NS; ++n) {
+                float pr[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    pr[j] = exp2_hw(s[n / 2][8 * (n % 2) + j] - ms);
+                    lpart += pr[j];
+                }
+                split_bf16x8(pr, phi[n], plo[n]);
+            }
+            if (!late) turn(t);
+            const uint16_t *vrow = sm_v[t & 1] + (4 * half + r16 / 4) * VP + 16 * ((lane / 16) % 2) + 4 * (r16 % 4);
+#pragma unroll
+            for (int n = 0; n < 2 * NS; ++n)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const uint2 a = lds_read_tr16(vrow + 16 * n * VP + 32 * mb);
+                    const uint2 b = lds_read_tr16(vrow + (16 * n + 8) * VP + 32 * mb);
+                    const bf16x8_t va = as_bf16x8(make_uint4(a.x, a.y, b.x, b.y));
+                    acc[mb] = mfma32(va, phi[n], acc[mb]);
+                    acc[mb] = mfma32(va, plo[n], acc[mb]);
+                }
+        }
+    } else {
+        for (int t = 0; t < n_tiles; ++t) turn(t);
+    }
+    const float lrun = lpart + shfl_xor_f(lpart, 32);
+    if (row0 + r32 < rows_total) {
+        // lane: row r32, dims 32mb + 8(i/4) + 4 half + i%4
+        float *dst = part + (((int64_t)g * n_splits + split) * rows_total + row0 + r32) * (D + kPartStride);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                float4 o = make_float4(acc[mb][4 * k] * v_scale, acc[mb][4 * k + 1] * v_scale,
+                                       acc[mb][4 * k + 2] * v_scale, acc[mb][4 * k + 3] * v_scale);
+                if (any_bad) o = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
+                *reinterpret_cast<float4 *>(dst + 32 * mb + 8 * k + 4 * half) = o;
+            }
+        if (half == 0) {
+            dst[D] = mref;
+            dst[D + 1] = lrun;
+        }
+    }
+}
+
 constexpr int kCombineThreads = 256;
 
 // One workgroup per (KV head, row).  The split weights 2^(m_s - M) are formed
@@ -1088,15 +1317,24 @@ hipError_t launch_mfma16(const AttnPlan &p, const float *q, const void *k_pool, 
     return hipGetLastError();
 }
 
-// rows per KV head from which K/V tiles are shared through LDS by 64-row groups
-constexpr int kRowsLds = 48;
-
-template <typename T, int D, int BT, int NW>
+template <typename T, int D, int BT, int NW, int TT>
 hipError_t launch_mfma_rows_nw(const AttnPlan &p, const float *q, const void *k_pool, const void *v_pool,
                                int64_t n_pages, const int32_t *view_pages, float qscale, float *part,
                                hipStream_t stream) {
+    dim3 grid(p.n_splits, p.n_kv_heads, (p.rows_per_head + NW * 32 - 1) / (NW * 32));
+    hipLaunchKernelGGL((attn_mfma_rows_kernel<T, D, BT, NW, TT>), grid, dim3(NW * kWave), 0, stream, q,
+                       static_cast<const T *>(k_pool), static_cast<const T *>(v_pool), n_pages, view_pages, p.n_sel,
+                       p.n_view, p.last_page_tokens, p.n_kv_heads, p.n_q_heads, p.group, p.rows_per_head,
+                       p.pages_per_split, p.n_splits, qscale, p.v_scale, part);
+    return hipGetLastError();
+}
+
+template <typename T, int D, int BT, int NW>
+hipError_t launch_mfma_rows16_nw(const AttnPlan &p, const float *q, const void *k_pool, const void *v_pool,
+                                 int64_t n_pages, const int32_t *view_pages, float qscale, float *part,
+                                 hipStream_t stream) {
     dim3 grid(p.n_splits, p.n_kv_heads, (p.rows_per_head + NW * kMfmaRows - 1) / (NW * kMfmaRows));
-    hipLaunchKernelGGL((attn_mfma_rows_kernel<T, D, BT, NW>), grid, dim3(NW * kWave), 0, stream, q,
+    hipLaunchKernelGGL((attn_mfma_rows16_kernel<T, D, BT, NW>), grid, dim3(NW * kWave), 0, stream, q,
                        static_cast<const T *>(k_pool), static_cast<const T *>(v_pool), n_pages, view_pages, p.n_sel,
                        p.n_view, p.last_page_tokens, p.n_kv_heads, p.n_q_heads, p.group, p.rows_per_head,
                        p.pages_per_split, p.n_splits, qscale, p.v_scale, part);
@@ -1107,11 +1345,12 @@ template <typename T, int D, int BT>
 hipError_t launch_mfma_rows(const AttnPlan &p, const float *q, const void *k_pool, const void *v_pool,
                             int64_t n_pages, const int32_t *view_pages, float qscale, float *part,
                             hipStream_t stream) {
-    if (p.rows_per_head <= 64)
-        return launch_mfma_rows_nw<T, D, BT, 4>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part, stream);
-    if (p.rows_per_head <= 128)
-        return launch_mfma_rows_nw<T, D, BT, 8>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part, stream);
-    return launch_mfma_rows_nw<T, D, BT, 16>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part, stream);
+    if (p.rows_per_head > kAttnRows32)
+        return launch_mfma_rows_nw<T, D, BT, kAttnRows32Waves, 64>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part,
+                                                                  stream);
+    if (p.rows_per_head > 64)
+        return launch_mfma_rows16_nw<T, D, BT, 8>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part, stream);
+    return launch_mfma_rows16_nw<T, D, BT, 4>(p, q, k_pool, v_pool, n_pages, view_pages, qscale, part, stream);
 }
 
 template <typename T, int D, int BT>
@@ -1120,12 +1359,12 @@ hipError_t launch_bt(const AttnPlan &p, const float *q, const void *k, const voi
     const int rows = p.rows_per_head;
     if constexpr (std::is_same<T, uint8_t>::value) {
         // FP8: always the matrix cores (rows padded to 16)
-        if (rows >= kRowsLds) return launch_mfma_rows<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
+        if (rows >= kAttnRowsLds) return launch_mfma_rows<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
         return launch_mfma16<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
     } else {
         if constexpr (std::is_same<T, uint16_t>::value) {
             // bf16 with 3 or more rows per KV head: matrix cores (rows padded to 16)
-            if (rows >= kRowsLds) return launch_mfma_rows<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
+            if (rows >= kAttnRowsLds) return launch_mfma_rows<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
             if (rows >= 3) return launch_mfma16<T, D, BT>(p, q, k, v, n_pages, vp, qscale, part, stream);
         }
         if constexpr (D / Vec16<T>::N == 16) {

@@ -175,19 +175,42 @@ struct AttnPlan {
     size_t total;
 };
 
+// Rows per KV head from which the bf16 and FP8 kernels share K/V tiles through
+// LDS.  Above kAttnRows32 rows, where the products set the time, workgroups of
+// eight 32-row waves with a compute unit to themselves (512 rows over 64K tokens: 241
+// against 285 us); up to it, where the K/V stream does, 16-row waves, of which two
+// workgroups share a unit (48 rows over 64K tokens: 60 against 77 us; 128 rows: 89 against 97).
+constexpr int kAttnRowsLds = 48;
+constexpr int kAttnRows32 = 128;
+constexpr int kAttnRows32Waves = 8;
+
+inline int attn_pages_per_split(const AttnPlan &p, long long target) {
+    const long long want = ((long long)p.n_view * p.n_kv_heads + target - 1) / target;
+    return (int)(want < kAttnMinPages ? kAttnMinPages : (want > kAttnMaxPages ? kAttnMaxPages : want));
+}
+
 inline void plan_attn_layout(AttnPlan &p) {
     // one workgroup per compute unit for decode (4 to 47 rows per KV head):
     // with two per unit the second one dispatched to each unit falls behind
     // the first and finishes alone, and the gather of random pages runs
     // slower with both resident (measured at 1M: 169.4 against 172.5 us per
     // call).  The many-row kernel keeps two per unit.
-    const long long target = p.rows_per_head >= 48 ? 2 * kAttnTargetGroups : kAttnTargetGroups;
-    long long want = ((long long)p.n_view * p.n_kv_heads + target - 1) / target;
-    int pps = (int)(want < kAttnMinPages ? kAttnMinPages : (want > kAttnMaxPages ? kAttnMaxPages : want));
+    const bool many = p.rows_per_head >= kAttnRowsLds;
+    int pps = attn_pages_per_split(p, many ? 2 * kAttnTargetGroups : kAttnTargetGroups);
+    const size_t splits_cap = (size_t)((p.n_view + pps - 1) / pps);  // what the workspace holds
+    if (p.rows_per_head > kAttnRows32 && p.kv_dtype != 0) {
+        // one workgroup per compute unit, counting the row groups of a split.  Fewer
+        // splits also mean fewer partial rows (512 rows over a 64K view: 138 MB of
+        // them with 64 splits, 35 MB with 16; their merge 27.6 against 11.5 us)
+        const int per_group = 32 * kAttnRows32Waves;
+        const long long target = kAttnTargetGroups / ((p.rows_per_head + per_group - 1) / per_group);
+        const int few = attn_pages_per_split(p, target > 1 ? target : 1);
+        if (few > pps) pps = few;
+    }
     p.pages_per_split = pps;
     p.n_splits = (p.n_view + pps - 1) / pps;
     p.off_part = 0;
-    p.total = align_up(sizeof(float) * (size_t)p.n_kv_heads * p.n_splits * p.rows_per_head *
+    p.total = align_up(sizeof(float) * (size_t)p.n_kv_heads * splits_cap * p.rows_per_head *
                        (p.head_dim + kPartStride));
 }
 

@@ -505,6 +505,31 @@ def test_many_rows_attention(case):
         np.testing.assert_array_equal(o2[:, keep], out.cpu().numpy()[:, keep])
 
 
+@pytest.mark.parametrize("rows,dt", [(48, "bf16"), (65, "fp8"), (129, "bf16"), (257, "bf16")])
+def test_many_rows_rising_scores(rows, dt):
+    """Scores that climb along the view, by less than the reference's slack a
+    tile and then by far more: accumulators are rescaled late and in the middle of
+    a split, and waves past the last row only load."""
+    cfg = W.small_config(n_kv_heads=1, n_q_heads=1, head_dim=64, block_tokens=16, kv_dtype=dt,
+                         kv_scale=float(np.float32(8 / 448)), history_tokens=160 * 16, recent_tokens=32,
+                         budget_tokens=130 * 16, n_q=rows, mode=W.MEAN_ALL)
+    w = W.generate(cfg, 52)
+    vp = np.arange(128, dtype=np.int32)[None]
+    q = np.ascontiguousarray(w.q[0, 0]) * np.float32(0.05)
+    q[..., 0] = 4.0
+    k = oracle_pool(cfg, w.k_pool[0]).copy() if dt == "fp8" else W.bf16_to_f32(w.k_pool[0])
+    k[:128, 0, :, 0] = np.linspace(-7.5, 7.5, 128, dtype=np.float32)[:, None]  # climbs by 0.04 base-2 units a token
+    k[100:, 0, :, 0] = 7.9
+    k[40:, 0, :, 1] += np.float32(1.5)
+    k_pool = W.fp8_codes(k, cfg.kv_scale) if dt == "fp8" else W.bf16_bits(k)
+    o_ref, l_ref = oracle.view_attention(q, oracle_pool(cfg, k_pool), oracle_pool(cfg, w.v_pool[0]), vp,
+                                         last_page_tokens=9)
+    st = LayerState(cfg, k_pool, w.v_pool[0], w.block_to_page, n_q=rows)
+    out, lse = st.attend(torch.from_numpy(q).cuda(), torch.from_numpy(vp).cuda(), last_page_tokens=9)
+    torch.cuda.synchronize()
+    check_attention(out.cpu().numpy(), lse.cpu().numpy(), o_ref, l_ref, dt)
+
+
 # ---- More than 65,536 candidates (histories beyond 1M tokens in 16-token
 # blocks; the Table 4 scalability range) -------------------------------------
 def test_4m_history_select():
