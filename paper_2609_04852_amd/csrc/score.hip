@@ -30,6 +30,12 @@ constexpr int kScoreThreads = 256;
 // 64*tile + i and accumulates its full dot products with the RH query rows of
 // the head.  For every 4-float slice of the head dimension the wave reads 1 KB
 // of contiguous index; the query values are the same for the whole wave.
+// What bounds it: the index stream.  In a model each layer's index is read once
+// per step, between other layers' K/V, so it comes from HBM: the loads carry the
+// non-temporal hint, and workgroups that follow each other take the KV heads of
+// one tile, which are adjacent in memory (at 1M, 266 MB: 56 us with plain loads
+// and a head's tiles in a row, 4.75 TB/s; 53 with the order alone, 50 with the hint alone,
+// 46 with both).
 template <int D, int RH, bool BATCH>
 __global__ __launch_bounds__(kScoreThreads) void score_logits_kernel(
     const float *__restrict__ q, const float *__restrict__ index, int n_blocks, int n_kv_heads,
@@ -46,57 +52,57 @@ __global__ __launch_bounds__(kScoreThreads) void score_logits_kernel(
     __shared__ float sm_m[NW][RH];
     __shared__ double sm_s[NW][RH];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int g = blockIdx.y, l = blockIdx.z;
-    const int tile = tile_lo + blockIdx.x * NW + wave;
-    const int64_t b = (int64_t)tile * kIndexTile + lane;
-    const int64_t c = b - n_sink;
-    const bool valid = blockIdx.x * NW + wave < n_tiles && c >= 0 && c < n_cand;
+    const int g = blockIdx.x, part = blockIdx.y, l = blockIdx.z;
 
     int64_t qrow[RH];
 #pragma unroll
     for (int r = 0; r < RH; ++r)
         qrow[r] = ((int64_t)l * n_q + r / group) * n_q_heads + g * group + r % group;
 
+    const int ti = part * NW + wave, tile = tile_lo + ti;
+    const int64_t c = (int64_t)tile * kIndexTile + lane - n_sink;
+    const bool valid = ti < n_tiles && c >= 0 && c < n_cand;
     float acc[RH];
 #pragma unroll
     for (int r = 0; r < RH; ++r) acc[r] = 0.f;
-    if (blockIdx.x * NW + wave < n_tiles) {
+    if (ti < n_tiles) {
         const int64_t tiles_per_layer = index_tiles(n_blocks);
         const float *src = index + (((int64_t)l * tiles_per_layer + tile) * n_kv_heads + g) *
                                        (int64_t)(D / 4) * (kIndexTile * 4) + lane * 4;
-        if constexpr (BATCH) {  // every load of the tile in flight at once
-            float4 xs[D / 4];
+        auto add = [&](int j4, const uint4 &w) {
+            const float4 x = make_float4(__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z),
+                                         __uint_as_float(w.w));
 #pragma unroll
-            for (int j4 = 0; j4 < D / 4; ++j4) xs[j4] = *reinterpret_cast<const float4 *>(src + j4 * (kIndexTile * 4));
+            for (int r = 0; r < RH; ++r) {
+                const float4 qv = *reinterpret_cast<const float4 *>(q + qrow[r] * D + j4 * 4);
+                acc[r] += qv.x * x.x + qv.y * x.y + qv.z * x.z + qv.w * x.w;
+            }
+        };
+        if constexpr (BATCH) {  // every load of the tile in flight at once
+            uint4 xs[D / 4];
+#pragma unroll
+            for (int j4 = 0; j4 < D / 4; ++j4) xs[j4] = load_stream16(src + j4 * (kIndexTile * 4));
             __builtin_amdgcn_sched_barrier(0);  // the scheduler keeps every load above the products
 #pragma unroll
-            for (int j4 = 0; j4 < D / 4; ++j4) {
-                const float4 x = xs[j4];
-#pragma unroll
-                for (int r = 0; r < RH; ++r) {
-                    const float4 qv = *reinterpret_cast<const float4 *>(q + qrow[r] * D + j4 * 4);
-                    acc[r] += qv.x * x.x + qv.y * x.y + qv.z * x.z + qv.w * x.w;
-                }
-            }
+            for (int j4 = 0; j4 < D / 4; ++j4) add(j4, xs[j4]);
         } else {
 #pragma unroll
-            for (int j4 = 0; j4 < D / 4; ++j4) {  // unrolled: the compiler keeps several loads in flight
-                const float4 x = *reinterpret_cast<const float4 *>(src + j4 * (kIndexTile * 4));
-#pragma unroll
-                for (int r = 0; r < RH; ++r) {
-                    const float4 qv = *reinterpret_cast<const float4 *>(q + qrow[r] * D + j4 * 4);
-                    acc[r] += qv.x * x.x + qv.y * x.y + qv.z * x.z + qv.w * x.w;
-                }
-            }
+            for (int j4 = 0; j4 < D / 4; ++j4)  // unrolled: the compiler keeps several loads in flight
+                add(j4, load_stream16(src + j4 * (kIndexTile * 4)));
         }
     }
-    // logits of this tile (rows contiguous over candidates), and per-wave stats
+    // logits of this tile (rows contiguous over candidates)
+    float s[RH];
 #pragma unroll
     for (int r = 0; r < RH; ++r) {
-        const float s = acc[r] * scale;
-        if (valid) logits[qrow[r] * cand_stride + c] = s;
-        float mx = wave_max(valid ? s : -INFINITY);
-        double e = (valid && mx != -INFINITY) ? (double)expf(s - mx) : 0.0;
+        s[r] = acc[r] * scale;
+        if (valid) logits[qrow[r] * cand_stride + c] = s[r];
+    }
+    // and the tile's stats
+#pragma unroll
+    for (int r = 0; r < RH; ++r) {
+        const float mx = wave_max(valid ? s[r] : -INFINITY);
+        double e = (valid && mx != -INFINITY) ? (double)expf(s[r] - mx) : 0.0;
         e = wave_sum_d(e);
         if (lane == 0) {
             sm_m[wave][r] = mx;
@@ -113,8 +119,8 @@ __global__ __launch_bounds__(kScoreThreads) void score_logits_kernel(
 #pragma unroll
         for (int w = 0; w < NW; ++w)
             if (sm_m[w][r] != -INFINITY) sum += sm_s[w][r] * exp((double)sm_m[w][r] - (double)mx);
-        tmax[qrow[r] * n_parts + blockIdx.x] = mx;
-        tsum[qrow[r] * n_parts + blockIdx.x] = sum;
+        tmax[qrow[r] * n_parts + part] = mx;
+        tsum[qrow[r] * n_parts + part] = sum;
     }
 }
 
@@ -955,19 +961,15 @@ __global__ __launch_bounds__(kScoreThreads) void score_reduce_kernel(
 template <int D, int RH>
 hipError_t launch_logits(const SelectPlan &p, const float *q, const float *index, float scale,
                          float *logits, float *tmax, double *tsum, uint32_t *hist, hipStream_t stream) {
-    dim3 grid(p.n_parts, p.n_kv_heads, p.n_layers);
+    dim3 grid(p.n_kv_heads, p.n_parts, p.n_layers);
     const int hist_words = p.fused_stats ? p.n_sel * kSelHistWords : 0;
-    if (p.batch_loads)
-        hipLaunchKernelGGL((score_logits_kernel<D, RH, true>), grid, dim3(kScoreThreads), 0, stream, q, index,
-                           p.n_blocks, p.n_kv_heads, p.n_q_heads, p.group, p.n_q, p.n_sink, p.n_cand,
-                           (int64_t)p.cand_stride, p.tile_lo, p.n_tiles, p.n_parts, scale, logits, tmax,
-                           tsum, hist, hist_words);
-    else
-        hipLaunchKernelGGL((score_logits_kernel<D, RH, false>), grid, dim3(kScoreThreads), 0, stream, q, index,
-                           p.n_blocks, p.n_kv_heads, p.n_q_heads, p.group, p.n_q, p.n_sink, p.n_cand,
-                           (int64_t)p.cand_stride, p.tile_lo, p.n_tiles, p.n_parts, scale, logits, tmax,
-                           tsum, hist, hist_words);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kScoreThreads), 0, stream, q, index, p.n_blocks, p.n_kv_heads,
+                           p.n_q_heads, p.group, p.n_q, p.n_sink, p.n_cand, (int64_t)p.cand_stride, p.tile_lo,
+                           p.n_tiles, p.n_parts, scale, logits, tmax, tsum, hist, hist_words);
+        return hipGetLastError();
+    };
+    return p.batch_loads ? go(score_logits_kernel<D, RH, true>) : go(score_logits_kernel<D, RH, false>);
 }
 
 template <int D, int WR, int WC, int NB>
