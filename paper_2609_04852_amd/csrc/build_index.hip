@@ -29,6 +29,15 @@ constexpr int kWaves = 4;
 // at 1M on two boxes; the plain build is 8% slower with half tiles)
 template <bool ROPE>
 constexpr int part_blocks() { return ROPE ? kIndexTile / 2 : kIndexTile; }
+// Ranges that give fewer than kPartGroups workgroups so (four per compute unit,
+// as many as reside) take parts of kSmallPart blocks: a wave then goes through 4
+// blocks in turn instead of 8 or 16, and their load round trips set such a build's time
+// (2,048 blocks x 8 heads of bf16 at d = 128: 18.7 -> 16.6 us, from encoded keys 24.5
+// -> 21.6; 600 encoded fp32 blocks of 64 tokens x 4 heads 35.9 -> 21.5).  With RoPE the
+// line falls with the block length, because every workgroup computes a table of that
+// many rows (752 workgroups at 64 tokens: 61.3 us, with small parts 62.2).
+constexpr int kSmallPart = 16;
+constexpr int64_t kPartGroups = 1024;
 
 // 4-byte load of raw keys read once (the non-temporal hint of load_stream16)
 template <typename T>
@@ -118,7 +127,7 @@ __device__ inline float rope_eps(int64_t p0, int t, double f) {
 // plain loop, so launches whose positions are known to stay below 2^26 leave
 // it out.  With ROPE the (cos, sin) table of t * f_j takes block_tokens * D/2
 // float2 of dynamic LDS.
-template <typename T, int D, bool ROPE, bool EPS>
+template <typename T, int D, bool ROPE, bool EPS, int kPart>
 __global__ __launch_bounds__(kWaves *kWave) void build_index_kernel(
     const T *__restrict__ k_pool, int64_t n_pages, const int32_t *__restrict__ block_to_page,
     int32_t first_block, int32_t n_blocks, int n_kv_heads, int block_tokens, float k_scale,
@@ -146,7 +155,6 @@ __global__ __launch_bounds__(kWaves *kWave) void build_index_kernel(
     constexpr int BPS0 = !ROPE ? 2 : (16 / NI > 4 ? 4 : 16 / NI);
     constexpr int BPS = !ROPE || BPS0 == 1 ? BPS0 : (!EPS ? 1 : BPS0 / 2);
     constexpr int RB = ROPE ? BPS : 1, RV = ROPE ? VEC / 2 : 1;  // sizes of the per-block rotation
-    constexpr int kPart = part_blocks<ROPE>();
     __shared__ float tile_buf[kPart * PAD];
     // RoPE: (cos, sin) of t * f_j, row t at pitch RP: a wave's reads (rows
     // tg, pairs lp * VEC/2 + e) then fall on distinct banks two lanes at a time
@@ -384,29 +392,34 @@ hipError_t launch_t(int n_kv_heads, int block_tokens, float k_scale, const void 
                     const int32_t *block_to_page, int32_t first_block, int32_t n_blocks,
                     float *index, hipStream_t stream, bool rope, const int64_t *block_pos,
                     const RopeFreqs *fr) {
-    const int part = rope ? part_blocks<true>() : part_blocks<false>();
+    const int big = rope ? part_blocks<true>() : part_blocks<false>();
+    const int64_t groups = ((int64_t)n_blocks + big - 1) / big * n_kv_heads;
+    const bool small = groups * (rope ? block_tokens / 16 : 1) < kPartGroups;
+    const int part = small ? kSmallPart : big;
     const int64_t t0 = first_block / part;
     const int64_t t1 = ((int64_t)first_block + n_blocks + part - 1) / part;
     dim3 grid((unsigned)(t1 - t0), (unsigned)n_kv_heads);
     RopeFreqs f{};
+    auto go = [&](auto kernel, size_t lds) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kWaves * kWave), lds, stream, static_cast<const T *>(k_pool), n_pages,
+                           block_to_page, first_block, n_blocks, n_kv_heads, block_tokens, k_scale, index, block_pos, f);
+    };
     if (rope) {
         f = *fr;
         const size_t lds = sizeof(float2) * (size_t)block_tokens * (D / 2 + 1);
         // default positions b * block_tokens all below 2^26: the rounding
         // correction is never taken, so leave it out of the kernel
         const bool near = block_pos == nullptr && ((int64_t)first_block + n_blocks) * block_tokens <= kEpsMinPos;
+        constexpr int kBig = part_blocks<true>();
         if (near)
-            hipLaunchKernelGGL((build_index_kernel<T, D, true, false>), grid, dim3(kWaves * kWave), lds, stream,
-                               static_cast<const T *>(k_pool), n_pages, block_to_page, first_block, n_blocks,
-                               n_kv_heads, block_tokens, k_scale, index, block_pos, f);
+            small ? go(build_index_kernel<T, D, true, false, kSmallPart>, lds)
+                  : go(build_index_kernel<T, D, true, false, kBig>, lds);
         else
-            hipLaunchKernelGGL((build_index_kernel<T, D, true, true>), grid, dim3(kWaves * kWave), lds, stream,
-                               static_cast<const T *>(k_pool), n_pages, block_to_page, first_block, n_blocks,
-                               n_kv_heads, block_tokens, k_scale, index, block_pos, f);
+            small ? go(build_index_kernel<T, D, true, true, kSmallPart>, lds)
+                  : go(build_index_kernel<T, D, true, true, kBig>, lds);
     } else {
-        hipLaunchKernelGGL((build_index_kernel<T, D, false, false>), grid, dim3(kWaves * kWave), 0, stream,
-                           static_cast<const T *>(k_pool), n_pages, block_to_page, first_block, n_blocks,
-                           n_kv_heads, block_tokens, k_scale, index, block_pos, f);
+        small ? go(build_index_kernel<T, D, false, false, kSmallPart>, 0)
+              : go(build_index_kernel<T, D, false, false, part_blocks<false>()>, 0);
     }
     return hipGetLastError();
 }

@@ -505,6 +505,39 @@ def test_many_rows_attention(case):
         np.testing.assert_array_equal(o2[:, keep], out.cpu().numpy()[:, keep])
 
 
+@pytest.mark.parametrize("dt,bt,rope", [("bf16", 16, False), ("bf16", 16, True), ("fp8", 16, False), ("f32", 32, True)])
+def test_index_pieces(dt, bt, rope):
+    """A whole build (large parts) against the same blocks in pieces (small parts)
+    that start and end inside, at and across the edges of tiles and parts:
+    bitwise equal, and nothing outside a piece is written."""
+    hkv, d, m = 8, 64, 9000 if bt == 16 else 4300
+    n_el = m * hkv * bt * d
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(n_el, generator=g, device="cuda")
+    pool = {"bf16": lambda: x.to(torch.bfloat16), "f32": lambda: x,
+            "fp8": lambda: (x * 16).clamp(-448, 448).to(torch.float8_e4m3fn)}[dt]().view(m, hkv, bt, d)
+    geom = K.Geom(hkv, hkv, d, bt, K.kv_dtype_of(pool), 0.0625, 0.0625)
+    b2p = torch.randperm(m, generator=g, device="cuda").to(torch.int32)
+    n = K.kvmem_index_bytes(geom, m) // 4
+    whole, parts = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+
+    def build(first, count, out):
+        if rope:
+            K.kvmem_build_index_rope(geom, pool, b2p, first, count, out, 1e6)
+        else:
+            K.kvmem_build_index(geom, pool, b2p, first, count, out)
+
+    build(0, m, whole)
+    at = 0
+    for i, count in enumerate([1, 14, 1, 16, 17, 15, 33, 63, 64, 65, 200, 3, 128]):
+        build(at, count, parts)
+        at += count
+        rows_w = K.index_rows(whole, m, hkv, d)
+        rows_p = K.index_rows(parts, m, hkv, d)
+        assert torch.equal(rows_p[:at].view(torch.int32), rows_w[:at].view(torch.int32)), (i, at)
+        assert not rows_p[at:].any(), (i, at)
+
+
 @pytest.mark.parametrize("rows,dt", [(48, "bf16"), (65, "fp8"), (129, "bf16"), (257, "bf16")])
 def test_many_rows_rising_scores(rows, dt):
     """Scores that climb along the view, by less than the reference's slack a
