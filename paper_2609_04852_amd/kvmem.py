@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import functools
 import os
 import re
 
@@ -54,6 +55,14 @@ class Geom:
     def c(self) -> kvmem_geom:
         return kvmem_geom(self.n_kv_heads, self.n_q_heads, self.head_dim, self.block_tokens,
                           self.kv_dtype, self.k_scale, self.v_scale)
+
+    @functools.cached_property
+    def ref(self):
+        """Pointer to this geometry's C struct, made once (the fields are frozen)."""
+        return ctypes.byref(self.c())
+
+    def __getstate__(self):  # copies and pickles hold the fields, not the pointer
+        return {f.name: getattr(self, f.name) for f in dataclasses.fields(self)}
 
 
 class kvmem_working_set(ctypes.Structure):
@@ -125,13 +134,15 @@ def _check(status: int):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
+    """The stream's handle; by default the current device's current stream, asked for
+    without building a Stream object (2 us a call)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def kv_dtype_of(t: torch.Tensor) -> int:
@@ -145,7 +156,7 @@ def kv_dtype_of(t: torch.Tensor) -> int:
 
 
 def _need(t: torch.Tensor, dtype, name: str):
-    if t.dtype != dtype or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype is not dtype or not t.is_contiguous() or not t.is_cuda:
         raise TypeError(f"{name} must be a contiguous CUDA {dtype} tensor")
 
 
@@ -153,7 +164,7 @@ INDEX_TILE = 64
 
 
 def kvmem_index_bytes(geom: Geom, n_blocks: int) -> int:
-    n = lib().kvmem_index_bytes(ctypes.byref(geom.c()), n_blocks)
+    n = lib().kvmem_index_bytes(geom.ref, n_blocks)
     if n == 0 and n_blocks > 0:
         raise KvmemError(-2, kvmem_last_error())
     return n
@@ -180,7 +191,7 @@ def kvmem_build_index(geom: Geom, k_pool: torch.Tensor, block_to_page: torch.Ten
     if index.numel() * 4 < kvmem_index_bytes(geom, first_block + n_blocks):
         raise ValueError("index is smaller than the block range needs")
     n_pages = k_pool.numel() // (geom.n_kv_heads * geom.block_tokens * geom.head_dim)
-    _check(lib().kvmem_build_index(ctypes.byref(geom.c()), _ptr(k_pool), n_pages,
+    _check(lib().kvmem_build_index(geom.ref, _ptr(k_pool), n_pages,
                                    _ptr(block_to_page), first_block, n_blocks, _ptr(index),
                                    _stream(stream)))
 
@@ -189,14 +200,14 @@ def kvmem_plan_view(geom: Geom, n_blocks: int, n_sink: int, n_recent: int,
                     model_ctx_tokens: int, gpu_kv_tokens: int) -> tuple[int, int]:
     k = ctypes.c_int32()
     n = ctypes.c_int32()
-    _check(lib().kvmem_plan_view(ctypes.byref(geom.c()), n_blocks, n_sink, n_recent,
+    _check(lib().kvmem_plan_view(geom.ref, n_blocks, n_sink, n_recent,
                                  model_ctx_tokens, gpu_kv_tokens, ctypes.byref(k), ctypes.byref(n)))
     return k.value, n.value
 
 
 def kvmem_select_workspace_bytes(geom: Geom, n_layers: int, n_q: int, n_blocks: int, n_sink: int,
                                  n_recent: int, mode: int) -> int:
-    n = lib().kvmem_select_workspace_bytes(ctypes.byref(geom.c()), n_layers, n_q, n_blocks, n_sink,
+    n = lib().kvmem_select_workspace_bytes(geom.ref, n_layers, n_q, n_blocks, n_sink,
                                            n_recent, mode)
     if n == 0:
         raise KvmemError(-2, kvmem_last_error())
@@ -230,7 +241,7 @@ def kvmem_select(geom: Geom, q: torch.Tensor, index: torch.Tensor, n_blocks: int
         if scores.numel() < n_sel * n_blocks:
             raise ValueError("scores is smaller than n_sel * n_blocks")
     out_n = ctypes.c_int32()
-    _check(lib().kvmem_select(ctypes.byref(geom.c()), n_layers, _ptr(q), n_q, _ptr(index), n_blocks,
+    _check(lib().kvmem_select(geom.ref, n_layers, _ptr(q), n_q, _ptr(index), n_blocks,
                               n_sink, n_recent, model_ctx_tokens, gpu_kv_tokens, mode, scale,
                               _ptr(block_to_page), _ptr(view_blocks), _ptr(view_pages), _ptr(scores),
                               ctypes.byref(out_n), _ptr(workspace), workspace.numel(),
@@ -268,7 +279,7 @@ def kvmem_select_noalloc(geom: Geom, q: torch.Tensor, index: torch.Tensor, n_blo
         if scores.numel() < n_sel * n_blocks:
             raise ValueError("scores is smaller than n_sel * n_blocks")
     out_n = ctypes.c_int32()
-    _check(lib().kvmem_select_noalloc(ctypes.byref(geom.c()), n_layers, _ptr(q), n_q, _ptr(index), n_blocks,
+    _check(lib().kvmem_select_noalloc(geom.ref, n_layers, _ptr(q), n_q, _ptr(index), n_blocks,
                                       n_sink, n_recent, model_ctx_tokens, gpu_kv_tokens, mode, scale,
                                       _ptr(block_to_page), _ptr(view_blocks), _ptr(view_pages), _ptr(scores),
                                       ctypes.byref(out_n), _stream(stream)))
@@ -276,7 +287,7 @@ def kvmem_select_noalloc(geom: Geom, q: torch.Tensor, index: torch.Tensor, n_blo
 
 
 def kvmem_sparse_attn_workspace_bytes(geom: Geom, n_q: int, n_sel: int, n_view: int) -> int:
-    n = lib().kvmem_sparse_attn_workspace_bytes(ctypes.byref(geom.c()), n_q, n_sel, n_view)
+    n = lib().kvmem_sparse_attn_workspace_bytes(geom.ref, n_q, n_sel, n_view)
     if n == 0:
         raise KvmemError(-2, kvmem_last_error())
     return n
@@ -309,7 +320,7 @@ def kvmem_sparse_attn(geom: Geom, q: torch.Tensor, k_pool: torch.Tensor, v_pool:
         if lse.numel() < n_q * geom.n_q_heads:
             raise ValueError("lse is smaller than n_q * Hq")
     n_pages = k_pool.numel() // (geom.n_kv_heads * geom.block_tokens * geom.head_dim)
-    _check(lib().kvmem_sparse_attn(ctypes.byref(geom.c()), _ptr(q), n_q, _ptr(k_pool), _ptr(v_pool),
+    _check(lib().kvmem_sparse_attn(geom.ref, _ptr(q), n_q, _ptr(k_pool), _ptr(v_pool),
                                    n_pages, _ptr(view_pages), n_sel, n_view, last_page_tokens, scale,
                                    _ptr(out), _ptr(lse), _ptr(workspace), workspace.numel(),
                                    _stream(stream)))
@@ -333,7 +344,7 @@ def kvmem_build_index_rope(geom: Geom, k_pool: torch.Tensor, block_to_page: torc
     if index.numel() * 4 < kvmem_index_bytes(geom, first_block + n_blocks):
         raise ValueError("index is smaller than the block range needs")
     n_pages = k_pool.numel() // (geom.n_kv_heads * geom.block_tokens * geom.head_dim)
-    _check(lib().kvmem_build_index_rope(ctypes.byref(geom.c()), _ptr(k_pool), n_pages, _ptr(block_to_page),
+    _check(lib().kvmem_build_index_rope(geom.ref, _ptr(k_pool), n_pages, _ptr(block_to_page),
                                         _ptr(block_pos), float(rope_base), first_block, n_blocks, _ptr(index),
                                         _stream(stream)))
 
@@ -352,7 +363,7 @@ def kvmem_materialize(geom: Geom, rope_base: float, raw_k_pool: torch.Tensor, v_
     n = src_pages.numel()
     if dst_pages.numel() != n or positions.numel() != n:
         raise ValueError("src_pages, dst_pages and positions must have the same length")
-    _check(lib().kvmem_materialize(ctypes.byref(geom.c()), float(rope_base), _ptr(raw_k_pool), _ptr(v_pool),
+    _check(lib().kvmem_materialize(geom.ref, float(rope_base), _ptr(raw_k_pool), _ptr(v_pool),
                                    raw_k_pool.shape[0], _ptr(src_pages), _ptr(positions), _ptr(dst_pages), n,
                                    _ptr(k_dst_pool), _ptr(v_dst_pool), k_dst_pool.shape[0], _stream(stream)))
 
@@ -366,7 +377,7 @@ def kvmem_rerope(geom: Geom, rope_base: float, k_pool: torch.Tensor, pages: torc
     _need(delta_positions, torch.int64, "delta_positions")
     if delta_positions.numel() != pages.numel():
         raise ValueError("pages and delta_positions must have the same length")
-    _check(lib().kvmem_rerope(ctypes.byref(geom.c()), float(rope_base), _ptr(k_pool), k_pool.shape[0],
+    _check(lib().kvmem_rerope(geom.ref, float(rope_base), _ptr(k_pool), k_pool.shape[0],
                               _ptr(pages), _ptr(delta_positions), pages.numel(), _stream(stream)))
 
 
@@ -419,7 +430,7 @@ def kvmem_working_set_update(geom: Geom, rope_base: float, ws: WorkingSetArrays,
     n_view = view_blocks.numel()
     if exec_pages.numel() < n_view or counts.numel() < 16:
         raise ValueError("exec_pages needs n_view entries and counts 16")
-    _check(lib().kvmem_working_set_update(ctypes.byref(geom.c()), float(rope_base), ctypes.byref(ws.c()), step,
+    _check(lib().kvmem_working_set_update(geom.ref, float(rope_base), ctypes.byref(ws.c()), step,
                                           _ptr(view_blocks), n_view, first_position, max_deltas,
                                           _ptr(block_to_page), _ptr(raw_k_pool), _ptr(v_pool), raw_k_pool.shape[0],
                                           _ptr(k_exec_pool), _ptr(v_exec_pool), _ptr(exec_pages), _ptr(counts),

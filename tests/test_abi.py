@@ -265,3 +265,17 @@ def test_working_set_validation(L):
     fp8 = ctypes.byref(g1(kv_dtype=K.KVMEM_FP8_E4M3, k_scale=0.02, v_scale=0.02))
     assert up(g=fp8) == "KVMEM_ERR_UNSUPPORTED"
     assert _status(L.kvmem_working_set_reset(None, None)) == "KVMEM_ERR_NULL"
+
+
+def test_geom_copies_after_use():
+    """The geometry's cached C pointer stays out of copies, pickles and comparisons."""
+    import copy
+    import dataclasses
+    import pickle
+
+    g = K.Geom(8, 32, 128, 16, K.KVMEM_FP8_E4M3, 0.5, 0.25)
+    fresh = K.Geom(8, 32, 128, 16, K.KVMEM_FP8_E4M3, 0.5, 0.25)
+    assert g.ref is g.ref and g == fresh and hash(g) == hash(fresh)
+    for h in (copy.copy(g), copy.deepcopy(g), pickle.loads(pickle.dumps(g))):
+        assert h == g and h.ref is not g.ref and h.ref._obj.k_scale == 0.5
+    assert dataclasses.replace(g, block_tokens=32).ref._obj.block_tokens == 32
