@@ -267,8 +267,8 @@ inline size_t ws_scratch_bytes(int n_view, int n_pages, WsScratch *w = nullptr, 
 
 // ---- launchers (return the launch status) -------------------------------
 // kv_dtype: 0 fp32, 1 bf16 bits, 2 FP8 E4M3 codes (scaled by k_scale, v_scale).
-// materialize / rope_delta: with n_dev set, the first *n_dev of the n list
-// entries are processed (the count is known on the device only).
+// rope_lists: the build and delta lists of a working-set update (their lengths
+// are known on the device only).
 // block_pos / fr are used only when rope is set: the keys carry RoPE at
 // positions block_pos[b] + t (block_pos NULL: b * block_tokens + t).
 hipError_t launch_build_index(int kv_dtype, int head_dim, int n_kv_heads, int block_tokens,
@@ -281,11 +281,15 @@ hipError_t launch_materialize(int kv_dtype, int head_dim, int n_kv_heads, int bl
                               const RopeFreqs &fr, const void *raw_k, const void *v_src,
                               int64_t n_src_pages, const int32_t *src_pages, const int64_t *positions,
                               const int32_t *dst_pages, int32_t n, void *k_dst, void *v_dst,
-                              int64_t n_dst_pages, hipStream_t stream, const int32_t *n_dev = nullptr);
+                              int64_t n_dst_pages, hipStream_t stream);
 
 hipError_t launch_rope_delta(int kv_dtype, int head_dim, int n_kv_heads, int block_tokens, const RopeFreqs &fr,
                              void *k_pool, int64_t n_pages, const int32_t *pages, const int64_t *delta,
-                             int32_t n, hipStream_t stream, const int32_t *n_dev = nullptr);
+                             int32_t n, hipStream_t stream);
+
+hipError_t launch_rope_lists(int kv_dtype, int head_dim, int n_kv_heads, int block_tokens, const RopeFreqs &fr,
+                             const void *raw_k, const void *v_src, int64_t n_src_pages, const WsScratch &w, int32_t n_view,
+                             void *k_exec, void *v_exec, int64_t n_pages, hipStream_t stream);
 
 hipError_t launch_ws_reset(const WorkingSetState &s, hipStream_t stream);
 

@@ -80,21 +80,17 @@ __device__ inline void rotate(float (&x0)[VEC], float (&x1)[VEC], const float2 *
     }
 }
 
+// Page dst of the execution pool from page src: K turned to positions p0 + t, V copied.
+// cs holds block_tokens * D/2 pairs.  The whole workgroup calls it.
 template <typename T, int D>
-__global__ __launch_bounds__(kRopeThreads) void rope_materialize_kernel(
-    const T *__restrict__ raw_k, const T *__restrict__ v_src, int64_t n_src_pages,
-    const int32_t *__restrict__ src_pages, const int64_t *__restrict__ positions,
-    const int32_t *__restrict__ dst_pages, T *__restrict__ k_dst, T *__restrict__ v_dst,
-    int64_t n_dst_pages, int n_kv_heads, int block_tokens, RopeFreqs fr, const int32_t *__restrict__ n_dev) {
+__device__ inline void materialize_page(const T *__restrict__ raw_k, const T *__restrict__ v_src, int64_t n_src_pages,
+                                        int64_t src, int64_t p0, int64_t dst, T *__restrict__ k_dst,
+                                        T *__restrict__ v_dst, int64_t n_dst_pages, int n_kv_heads, int block_tokens,
+                                        const RopeFreqs &fr, float2 *cs) {
     using L = Lanes<T>;
     constexpr int VEC = L::VEC, HL = D / 2 / VEC;  // lanes per half row
-    __shared__ float2 cs[kMaxBt * (D / 2)];        // (cos, sin) per (token, pair), shared by the heads
-    const int i = blockIdx.x;
-    if (n_dev && i >= *n_dev) return;  // the list's length is known on the device only
-    const int64_t src = src_pages[i], dst = dst_pages[i];
     if (dst < 0 || dst >= n_dst_pages) return;  // nowhere to write
     const bool src_ok = src >= 0 && src < n_src_pages;
-    const int64_t p0 = positions[i];
     for (int k = threadIdx.x; k < block_tokens * (D / 2); k += kRopeThreads) {
         float c, sn;
         rope_cos_sin(p0 + k / (D / 2), fr.f[k % (D / 2)], &c, &sn);
@@ -129,18 +125,14 @@ __global__ __launch_bounds__(kRopeThreads) void rope_materialize_kernel(
     }
 }
 
+// K of one page turned in place by dp positions (cs: D/2 pairs; every token of the
+// page turns by the same angles).
 template <typename T, int D>
-__global__ __launch_bounds__(kRopeThreads) void rope_delta_kernel(
-    T *__restrict__ k_pool, int64_t n_pages, const int32_t *__restrict__ pages,
-    const int64_t *__restrict__ delta, int n_kv_heads, int block_tokens, RopeFreqs fr,
-    const int32_t *__restrict__ n_dev) {
+__device__ inline void delta_page(T *__restrict__ k_pool, int64_t n_pages, int64_t page, int64_t dp, int n_kv_heads,
+                                  int block_tokens, const RopeFreqs &fr, float2 *cs) {
     using L = Lanes<T>;
     constexpr int VEC = L::VEC, HL = D / 2 / VEC;
-    __shared__ float2 cs[D / 2];  // every token of the page turns by the same angles
-    if (n_dev && (int)blockIdx.x >= *n_dev) return;
-    const int64_t page = pages[blockIdx.x];
     if (page < 0 || page >= n_pages) return;
-    const int64_t dp = delta[blockIdx.x];
     for (int k = threadIdx.x; k < D / 2; k += kRopeThreads) {
         float c, sn;
         rope_cos_sin(dp, fr.f[k], &c, &sn);
@@ -162,36 +154,71 @@ __global__ __launch_bounds__(kRopeThreads) void rope_delta_kernel(
     }
 }
 
+template <typename T, int D>
+__global__ __launch_bounds__(kRopeThreads) void rope_materialize_kernel(
+    const T *__restrict__ raw_k, const T *__restrict__ v_src, int64_t n_src_pages,
+    const int32_t *__restrict__ src_pages, const int64_t *__restrict__ positions,
+    const int32_t *__restrict__ dst_pages, T *__restrict__ k_dst, T *__restrict__ v_dst,
+    int64_t n_dst_pages, int n_kv_heads, int block_tokens, RopeFreqs fr) {
+    __shared__ float2 cs[kMaxBt * (D / 2)];  // (cos, sin) per (token, pair), shared by the heads
+    const int i = blockIdx.x;
+    materialize_page<T, D>(raw_k, v_src, n_src_pages, src_pages[i], positions[i], dst_pages[i], k_dst, v_dst,
+                           n_dst_pages, n_kv_heads, block_tokens, fr, cs);
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(kRopeThreads) void rope_delta_kernel(
+    T *__restrict__ k_pool, int64_t n_pages, const int32_t *__restrict__ pages,
+    const int64_t *__restrict__ delta, int n_kv_heads, int block_tokens, RopeFreqs fr) {
+    __shared__ float2 cs[D / 2];
+    delta_page<T, D>(k_pool, n_pages, pages[blockIdx.x], delta[blockIdx.x], n_kv_heads, block_tokens, fr, cs);
+}
+
+// The re-encodings of a working-set update, whose list lengths are known on the
+// device only: workgroup i takes entry i of the build list, then of the delta
+// list (a view block is in at most one, so n_view workgroups do).  As two
+// launches each list left most of its n_view workgroups with nothing and drained
+// by itself (512 loads and 1,536 turned pages of 64 KB: 36 + 39 us).
+template <typename T, int D>
+__global__ __launch_bounds__(kRopeThreads) void rope_lists_kernel(
+    const T *__restrict__ raw_k, const T *__restrict__ v_src, int64_t n_src_pages, WsScratch w, T *__restrict__ k_exec,
+    T *__restrict__ v_exec, int64_t n_pages, int n_kv_heads, int block_tokens, RopeFreqs fr) {
+    __shared__ float2 cs[kMaxBt * (D / 2)];
+    const int i = blockIdx.x, n_build = w.lists[0], j = i - n_build;
+    if (i < n_build)
+        materialize_page<T, D>(raw_k, v_src, n_src_pages, w.build_src[i], w.build_pos[i], w.build_dst[i], k_exec, v_exec,
+                               n_pages, n_kv_heads, block_tokens, fr, cs);
+    else if (j < w.lists[1])
+        delta_page<T, D>(k_exec, n_pages, w.delta_page[j], w.delta_shift[j], n_kv_heads, block_tokens, fr, cs);
+}
+
 template <int D>
 hipError_t materialize_d(int kv_dtype, const void *raw_k, const void *v_src, int64_t n_src_pages,
                          const int32_t *src_pages, const int64_t *positions, const int32_t *dst_pages,
                          int32_t n, void *k_dst, void *v_dst, int64_t n_dst_pages, int n_kv_heads,
-                         int block_tokens, const RopeFreqs &fr, hipStream_t stream, const int32_t *n_dev) {
+                         int block_tokens, const RopeFreqs &fr, hipStream_t stream) {
     if (kv_dtype == 1)
         hipLaunchKernelGGL((rope_materialize_kernel<uint16_t, D>), dim3(n), dim3(kRopeThreads), 0, stream,
                            static_cast<const uint16_t *>(raw_k), static_cast<const uint16_t *>(v_src),
                            n_src_pages, src_pages, positions, dst_pages, static_cast<uint16_t *>(k_dst),
-                           static_cast<uint16_t *>(v_dst), n_dst_pages, n_kv_heads, block_tokens, fr, n_dev);
+                           static_cast<uint16_t *>(v_dst), n_dst_pages, n_kv_heads, block_tokens, fr);
     else
         hipLaunchKernelGGL((rope_materialize_kernel<float, D>), dim3(n), dim3(kRopeThreads), 0, stream,
                            static_cast<const float *>(raw_k), static_cast<const float *>(v_src), n_src_pages,
                            src_pages, positions, dst_pages, static_cast<float *>(k_dst),
-                           static_cast<float *>(v_dst), n_dst_pages, n_kv_heads, block_tokens, fr, n_dev);
+                           static_cast<float *>(v_dst), n_dst_pages, n_kv_heads, block_tokens, fr);
     return hipGetLastError();
 }
 
 template <int D>
 hipError_t delta_d(int kv_dtype, void *k_pool, int64_t n_pages, const int32_t *pages, const int64_t *delta,
-                   int32_t n, int n_kv_heads, int block_tokens, const RopeFreqs &fr, hipStream_t stream,
-                   const int32_t *n_dev) {
+                   int32_t n, int n_kv_heads, int block_tokens, const RopeFreqs &fr, hipStream_t stream) {
     if (kv_dtype == 1)
         hipLaunchKernelGGL((rope_delta_kernel<uint16_t, D>), dim3(n), dim3(kRopeThreads), 0, stream,
-                           static_cast<uint16_t *>(k_pool), n_pages, pages, delta, n_kv_heads, block_tokens, fr,
-                           n_dev);
+                           static_cast<uint16_t *>(k_pool), n_pages, pages, delta, n_kv_heads, block_tokens, fr);
     else
         hipLaunchKernelGGL((rope_delta_kernel<float, D>), dim3(n), dim3(kRopeThreads), 0, stream,
-                           static_cast<float *>(k_pool), n_pages, pages, delta, n_kv_heads, block_tokens, fr,
-                           n_dev);
+                           static_cast<float *>(k_pool), n_pages, pages, delta, n_kv_heads, block_tokens, fr);
     return hipGetLastError();
 }
 
@@ -201,23 +228,40 @@ hipError_t launch_materialize(int kv_dtype, int head_dim, int n_kv_heads, int bl
                               const RopeFreqs &fr, const void *raw_k, const void *v_src,
                               int64_t n_src_pages, const int32_t *src_pages, const int64_t *positions,
                               const int32_t *dst_pages, int32_t n, void *k_dst, void *v_dst,
-                              int64_t n_dst_pages, hipStream_t stream, const int32_t *n_dev) {
+                              int64_t n_dst_pages, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     return head_dim == 128
                ? materialize_d<128>(kv_dtype, raw_k, v_src, n_src_pages, src_pages, positions, dst_pages, n,
-                                    k_dst, v_dst, n_dst_pages, n_kv_heads, block_tokens, fr, stream, n_dev)
+                                    k_dst, v_dst, n_dst_pages, n_kv_heads, block_tokens, fr, stream)
                : materialize_d<64>(kv_dtype, raw_k, v_src, n_src_pages, src_pages, positions, dst_pages, n,
-                                   k_dst, v_dst, n_dst_pages, n_kv_heads, block_tokens, fr, stream, n_dev);
+                                   k_dst, v_dst, n_dst_pages, n_kv_heads, block_tokens, fr, stream);
 }
 
 hipError_t launch_rope_delta(int kv_dtype, int head_dim, int n_kv_heads, int block_tokens, const RopeFreqs &fr,
                              void *k_pool, int64_t n_pages, const int32_t *pages, const int64_t *delta,
-                             int32_t n, hipStream_t stream, const int32_t *n_dev) {
+                             int32_t n, hipStream_t stream) {
     if (n == 0) return hipSuccess;
     return head_dim == 128 ? delta_d<128>(kv_dtype, k_pool, n_pages, pages, delta, n, n_kv_heads, block_tokens,
-                                          fr, stream, n_dev)
+                                          fr, stream)
                            : delta_d<64>(kv_dtype, k_pool, n_pages, pages, delta, n, n_kv_heads, block_tokens,
-                                         fr, stream, n_dev);
+                                         fr, stream);
+}
+
+hipError_t launch_rope_lists(int kv_dtype, int head_dim, int n_kv_heads, int block_tokens, const RopeFreqs &fr,
+                             const void *raw_k, const void *v_src, int64_t n_src_pages, const WsScratch &w, int32_t n_view,
+                             void *k_exec, void *v_exec, int64_t n_pages, hipStream_t stream) {
+    if (n_view == 0) return hipSuccess;
+    auto go = [&](auto elem, auto dim) {
+        using T = decltype(elem);
+        hipLaunchKernelGGL((rope_lists_kernel<T, decltype(dim)::value>), dim3(n_view), dim3(kRopeThreads), 0, stream,
+                           static_cast<const T *>(raw_k), static_cast<const T *>(v_src), n_src_pages, w,
+                           static_cast<T *>(k_exec), static_cast<T *>(v_exec), n_pages, n_kv_heads, block_tokens, fr);
+        return hipGetLastError();
+    };
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    if (kv_dtype == 1) return head_dim == 128 ? go(uint16_t{}, D128{}) : go(uint16_t{}, D64{});
+    return head_dim == 128 ? go(float{}, D128{}) : go(float{}, D64{});
 }
 
 }  // namespace kvmem

@@ -21,9 +21,8 @@
 //                updated, and the build list (misses and rebuilds: raw K
 //                re-encoded, V copied) and the delta list are filled
 //
-// The build and delta lists then run through the re-encoding kernels of
-// rope.hip, whose grids are sized for the whole view and stop at the lists'
-// device-side lengths.
+// The build and delta lists then run through one launch of rope.hip, whose grid is
+// sized for the whole view and stops at the lists' device-side lengths.
 #include "kvmem_device.h"
 #include "kvmem_internal.h"
 
@@ -221,11 +220,8 @@ hipError_t launch_ws_update(const WorkingSetState &s, const WsScratch &w, int kv
     hipLaunchKernelGGL(ws_apply_kernel, dim3(gv), dim3(kWsThreads), 0, stream, s, view, block_to_page, n_view,
                        first_pos, block_tokens, step, w, exec_pages);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_materialize(kv_dtype, head_dim, n_kv_heads, block_tokens, fr, raw_k, v_src, n_src_pages, w.build_src,
-                           w.build_pos, w.build_dst, n_view, k_exec, v_exec, s.n_pages, stream, w.lists);
-    if (e != hipSuccess) return e;
-    return launch_rope_delta(kv_dtype, head_dim, n_kv_heads, block_tokens, fr, k_exec, s.n_pages, w.delta_page,
-                             w.delta_shift, n_view, stream, w.lists + 1);
+    return launch_rope_lists(kv_dtype, head_dim, n_kv_heads, block_tokens, fr, raw_k, v_src, n_src_pages, w, n_view,
+                             k_exec, v_exec, s.n_pages, stream);
 }
 
 }  // namespace kvmem
