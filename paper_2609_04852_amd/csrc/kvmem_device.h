@@ -24,7 +24,13 @@ __device__ inline uint4 load_stream16(const T *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// The same for 8 bytes.
+// 16-byte store of data that is not read again before the caches turn over.
+template <typename T>
+__device__ inline void store_stream16(T *p, const uint4 &v) {
+    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t *>(p));
+}
+
+// The load for 8 bytes.
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ inline uint2 load_stream8(const T *p) {
