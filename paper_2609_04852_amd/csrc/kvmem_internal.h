@@ -29,8 +29,8 @@ __host__ __device__ inline int64_t index_layer_floats(int64_t n_blocks, int n_kv
 // wave), of the 16-row kernel (each wave takes one 16-block group of each),
 // and of the kernel for more rows.  Up to kScoreVectorRows query rows per KV
 // head are scored on the vector units, 9 to 16 on the 16-row matrix-core
-// kernel (rows past the head's count padded with zero queries), more by
-// 16-row chunks.
+// kernel (rows past the head's count padded with zero queries), more on the
+// int8 matrix cores in 32-row waves.
 constexpr int kScoreTilesPerGroup = 4;
 constexpr int kScoreVectorRows = 8;
 // The 16-row kernel's waves are persistent: about kMfma16Waves of them over
@@ -194,7 +194,7 @@ inline void plan_attn_layout(AttnPlan &p) {
     // with two per unit the second one dispatched to each unit falls behind
     // the first and finishes alone, and the gather of random pages runs
     // slower with both resident (measured at 1M: 169.4 against 172.5 us per
-    // call).  The many-row kernel keeps two per unit.
+    // call).  The kernel for 48 to 128 rows keeps two per unit.
     const bool many = p.rows_per_head >= kAttnRowsLds;
     int pps = attn_pages_per_split(p, many ? 2 * kAttnTargetGroups : kAttnTargetGroups);
     const size_t splits_cap = (size_t)((p.n_view + pps - 1) / pps);  // what the workspace holds
