@@ -29,15 +29,14 @@ constexpr int kWaves = 4;
 // at 1M on two boxes; the plain build is 8% slower with half tiles)
 template <bool ROPE>
 constexpr int part_blocks() { return ROPE ? kIndexTile / 2 : kIndexTile; }
-// Ranges that give fewer than kPartGroups workgroups so (four per compute unit,
-// as many as reside) take parts of kSmallPart blocks: a wave then goes through 4
-// blocks in turn instead of 8 or 16, and their load round trips set such a build's time
-// (2,048 blocks x 8 heads of bf16 at d = 128: 18.7 -> 16.6 us, from encoded keys 24.5
-// -> 21.6; 600 encoded fp32 blocks of 64 tokens x 4 heads 35.9 -> 21.5).  With RoPE the
-// line falls with the block length, because every workgroup computes a table of that
-// many rows (752 workgroups at 64 tokens: 61.3 us, with small parts 62.2).
+// Ranges that give fewer workgroups than these take parts of kSmallPart blocks: a
+// wave then goes through 4 blocks in turn instead of 8 or 16, and their load round
+// trips set such a build's time.  Plain (bf16, d = 128, 8 heads): 256 workgroups 18.7
+// -> 16.6 us, 320 24.4 -> 22.7, 376 25.2 -> 25.5, 512 27.6 -> 31.5.  From encoded
+// keys: 520 24.5 -> 21.1, 752 25.9 -> 25.7, 1,000 31.4 -> 33; there the line falls with the
+// block length, because every workgroup computes a table of that many rows.
 constexpr int kSmallPart = 16;
-constexpr int64_t kPartGroups = 1024;
+constexpr int64_t kPartGroups = 352, kPartGroupsRope = 704;
 
 // 4-byte load of raw keys read once (the non-temporal hint of load_stream16)
 template <typename T>
@@ -398,7 +397,7 @@ hipError_t launch_t(int n_kv_heads, int block_tokens, float k_scale, const void 
                     const RopeFreqs *fr) {
     const int big = rope ? part_blocks<true>() : part_blocks<false>();
     const int64_t groups = ((int64_t)n_blocks + big - 1) / big * n_kv_heads;
-    const bool small = groups * (rope ? block_tokens / 16 : 1) < kPartGroups;
+    const bool small = rope ? groups * (block_tokens / 16) < kPartGroupsRope : groups < kPartGroups;
     const int part = small ? kSmallPart : big;
     const int64_t t0 = first_block / part;
     const int64_t t1 = ((int64_t)first_block + n_blocks + part - 1) / part;
